@@ -372,8 +372,9 @@ ttie_status ttie_pcg_coupled(ttie_ctx* ctx, int64_t n_rows, const int32_t* row_p
 enum {
   TTIE_PARAM_SCREEN_BLOCKS = 0, /* blocks of the screening kernels: 64 .. 65536 (default 4096) */
   TTIE_PARAM_ROW_BLOCKS = 1,    /* blocks of ttie_bsr_symbolic's row kernel: 64 .. 65536 (default 2048) */
-  TTIE_PARAM_TRAV_BUDGET = 2,   /* nodes a traversal lane visits before a whole wave takes over its
-                                   query: 16 .. 2^20 (default 128) */
+  TTIE_PARAM_TRAV_BUDGET = 2,   /* work of a traversal wave (three units for 16 nodes visited or 64
+                                   pairs tested) before it hands the rest of its search to other
+                                   waves: 16 .. 2^20 (default 128) */
   TTIE_PARAM_HASH_BUDGET = 3,   /* later bucket entries a hash thread tests before a whole wave takes
                                    over the rest: 16 .. 2^20 (default 64) */
   TTIE_PARAM_SCREEN_TILE = 4,   /* candidates per tile of the screening's tile queue: a multiple of
@@ -402,9 +403,9 @@ ttie_status ttie_axpy(ttie_ctx* ctx, int64_t n_verts, double alpha, const double
 enum {
   TTIE_STAGE_BP_BOXES = 0,    /* triangle boxes, scene bounds, Morton bucket ranks (spatial hash: cells) */
   TTIE_STAGE_BP_SORT = 1,     /* counting sort by Morton bucket (spatial hash: by cell hash) */
-  TTIE_STAGE_BP_BUILD = 2,    /* leaf records and the implicit 4-ary tree's boxes, bottom up */
+  TTIE_STAGE_BP_BUILD = 2,    /* sorted leaves and the implicit 4-ary tree's boxes, bottom up */
   TTIE_STAGE_BP_TRAVERSE = 3, /* tree self-traversal / hash buckets / brute force, pair emission
-                                 (the queries over the traversal budget go on in TTIE_STAGE_BP_HEAVY) */
+                                 (searches over the traversal budget go on in TTIE_STAGE_BP_HEAVY) */
   TTIE_STAGE_SCREEN = 4,      /* per-candidate screening with FP64 filters */
   TTIE_STAGE_SCREEN_EXACT = 5,/* re-screening of the deferred candidates with exact predicates */
   TTIE_STAGE_DERIVS = 6,      /* per-hit interval gradients, energy, gradient, Hessian core */

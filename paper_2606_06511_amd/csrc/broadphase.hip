@@ -10,20 +10,15 @@
 //                  rank inside its bucket from the counting atomic
 //   scan, scatter  counting sort of the triangles by bucket (order inside a bucket arbitrary)
 //   k_levels       an implicit complete 4-ary tree over the sorted leaves: node (l, k) covers
-//                  leaves [k 4^l, (k+1) 4^l); boxes are reduced level by level in LDS, four
-//                  levels per launch from the leaves, five per launch above, so building needs
-//                  no atomics and no fences.  The first launch also writes the sorted leaf
-//                  records (FP64 box, vertex ids).  Each inner node also records a vertex
-//                  all its triangles hold, if there is one.
-//   k_traverse     two lanes per leaf s (its own 256-leaf subtree, staged in LDS, and the rest
-//                  of the tree), depth first over the subtrees holding leaves after s,
-//                  four child boxes per visit and a 64-bit mask stack, descending where the
-//                  FP32 boxes (rounded outwards) overlap, so every unordered pair is reported
-//                  once; a leaf is confirmed by the exact closed FP64 box test and the
-//                  shared-vertex test; pairs are staged per wave in LDS (ballot + mbcnt) and
-//                  flushed with one atomic per full buffer
-//   k_traverse_heavy  the searches k_traverse deferred, a wave's lanes sharing one stack of
-//                  nodes; a subtree whose triangles all hold a vertex of the query is skipped
+//                  leaves [k 4^l, (k+1) 4^l); FP32 boxes (rounded outwards) are reduced level by
+//                  level in LDS, four levels per launch from the leaves, five per launch above,
+//                  so building needs no atomics and no fences.  The first launch also writes the
+//                  sorted leaves' vertex ids.  Each inner node also records a vertex all its
+//                  triangles hold, if there is one.
+//   k_traverse     a wave per group of 64 consecutive leaves searches the tree once for all of
+//                  them and tests the leaves it meets against the 64 queries; a pair is confirmed
+//                  by the exact closed FP64 box test and the shared-vertex test
+//   k_traverse_heavy  the candidate batches and nodes that waves over their budget handed over
 //   k_brute        all i < j without a shared vertex (no box test)
 
 #include "internal.h"
@@ -48,6 +43,7 @@ __global__ void k_bp_init(Counters* c, unsigned long long* npairs) {
     *npairs = 0;
     c->n_entries = 0;
     c->n_heavy = 0;
+    c->n_batches = 0;
   }
 }
 
@@ -60,6 +56,7 @@ __global__ void __launch_bounds__(kBpBlock) k_tri_boxes(const double* __restrict
     *npairs = 0;
     ctr->n_entries = 0;
     ctr->n_heavy = 0;
+    ctr->n_batches = 0;
   }
   __shared__ uint32_t smin[3][kBpBlock], smax[3][kBpBlock];
   __shared__ double sext[kBpBlock];
@@ -247,7 +244,6 @@ __global__ void __launch_bounds__(kBpBlock) k_scatter(int64_t nt, int64_t nbucke
 // (l-1, 4k .. 4k+3), contiguous in memory; level L (m[L] = 1) is the root.
 struct Levels {
   int L;
-  int lt;  // levels lt..L are staged in LDS by the traversal (lt > L: none)
   int64_t m[24];
   int64_t off[24];
 };
@@ -256,10 +252,8 @@ struct Levels {
 // bits of an int32: a vertex id that every triangle of the node's subtree holds, or kNoCommon
 // (kEmpty for a node with no leaves, the identity of the merge).  A query that holds that
 // vertex shares it with every leaf below, so none of them can be its candidate (Sec. 1: pairs
-// with a shared vertex are adjacent), and k_traverse_heavy skips the subtree: the deferred
-// searches are mostly those of fans of thin triangles around one vertex, whose boxes all
-// overlap.  (k_traverse does not test it: the extra compares cost its every visit more than
-// the few fan queries it meets save.)
+// with a shared vertex are adjacent), and a group of queries that all hold it skips the subtree:
+// the boxes of a fan of thin triangles around one vertex all overlap.
 struct Box32 {
   float lo[4];
   float hi[4];
@@ -272,16 +266,8 @@ __device__ __forceinline__ void set_common(Box32& b, int32_t v) { b.lo[3] = __in
 __device__ __forceinline__ int32_t merge_common(int32_t a, int32_t b) {
   return a == kEmpty ? b : (b == kEmpty ? a : (a == b ? a : kNoCommon));
 }
-// Whether a query with vertex ids q skips the subtree of inner node b (never with the
-// vertex-adjacent option, under which one shared vertex does not make a pair adjacent).
-__device__ __forceinline__ bool skip_common(const Box32& b, const int32_t q[3], bool va) {
-  const int32_t v = box_common(b);
-  return !va & (v >= 0) & ((v == q[0]) | (v == q[1]) | (v == q[2]));
-}
-
-// sorted leaf record: the triangle's FP64 box, its vertex ids and its index
-struct LeafRec {
-  double lo[3], hi[3];
+// what a sorted leaf holds besides its FP32 box: the triangle's vertex ids and its index
+struct __align__(16) LeafIds {
   int32_t v[3];
   int32_t tri;
 };
@@ -320,7 +306,7 @@ template <int kThreads>
 __global__ void __launch_bounds__(kThreads) k_levels(int l0, Levels lv, const double* __restrict__ tbox,
                                                      const int32_t* __restrict__ ids,
                                                      const int32_t* __restrict__ tris, Box32* __restrict__ boxes,
-                                                     LeafRec* __restrict__ leaves, const int64_t* __restrict__ tri_off,
+                                                     LeafIds* __restrict__ leaves, const int64_t* __restrict__ tri_off,
                                                      int n_prob, int mbits, const int32_t* __restrict__ offset,
                                                      int32_t* __restrict__ qend) {
   __shared__ Box32 sh[kThreads];
@@ -337,12 +323,10 @@ __global__ void __launch_bounds__(kThreads) k_levels(int l0, Levels lv, const do
   if (k < lv.m[l0]) {
     if (l0 == 0) {
       const int32_t t = ids[k];
-      LeafRec r;
+      LeafIds r;
       for (int c = 0; c < 3; ++c) {
-        r.lo[c] = tbox[6 * (int64_t)t + c];
-        r.hi[c] = tbox[6 * (int64_t)t + 3 + c];
-        bx.lo[c] = __double2float_rd(r.lo[c]);
-        bx.hi[c] = __double2float_ru(r.hi[c]);
+        bx.lo[c] = __double2float_rd(tbox[6 * (int64_t)t + c]);
+        bx.hi[c] = __double2float_ru(tbox[6 * (int64_t)t + 3 + c]);
         r.v[c] = tris[3 * (int64_t)t + c];
       }
       r.tri = t;
@@ -387,16 +371,32 @@ __global__ void __launch_bounds__(kThreads) k_levels(int l0, Levels lv, const do
   }
 }
 
-__device__ __forceinline__ bool overlap32(const float q[6], const Box32& b) {
-  return q[0] <= b.hi[0] && b.lo[0] <= q[3] && q[1] <= b.hi[1] && b.lo[1] <= q[4] && q[2] <= b.hi[2] &&
-         b.lo[2] <= q[5];
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// number of set bits of m below this lane
+__device__ __forceinline__ int rank_below(uint64_t m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// inclusive prefix sum over the wave's lanes (row shifts, then the rows' last lanes broadcast)
+__device__ __forceinline__ int wave_incl_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+  return v;
 }
 
 // Per-wave LDS staging of emitted pairs.  Each step every lane of the wave offers at most one
 // pair; positions come from a ballot and the lanes below (mbcnt), so the staging needs no
 // atomics.  Only a flush -- when the wave's buffer is nearly full, and once at the end --
 // reserves global space, with one atomic for the whole buffer.
-constexpr int kEmitCap = 128;
+constexpr int kEmitCap = 128;  // of the hash kernels' waves
 
 // Where emitted pairs go: the pair array, its capacity, the caller's pair count (the
 // reservation counter itself, zeroed at the start of the broad phase) and the status word.
@@ -414,8 +414,9 @@ __device__ __forceinline__ int64_t sink_reserve(const PairSink& o, uint32_t n) {
   return base;
 }
 
+template <int kCap>
 struct WaveEmitter {
-  int2* buf;       // this wave's kEmitCap slots in LDS
+  int2* buf;       // this wave's kCap slots in LDS
   int count;       // wave-uniform fill level
 
   __device__ __forceinline__ void flush(const PairSink& o) {
@@ -442,14 +443,14 @@ struct WaveEmitter {
       buf[count + __popcll(mask & ((1ull << lane) - 1ull))] = make_int2(min(a, b), max(a, b));
     }
     count += __popcll(mask);
-    if (count > kEmitCap - 64) flush(o);
+    if (count > kCap - 64) flush(o);
   }
 };
 
 // End of an emitting kernel: one atomic reserves the space of all the block's waves (every
 // thread of the block must arrive here).
-template <int kWaves>
-__device__ __forceinline__ void block_flush(WaveEmitter& em, int* wcount, int64_t* bbase, const PairSink& o) {
+template <int kWaves, int kCap>
+__device__ __forceinline__ void block_flush(WaveEmitter<kCap>& em, int* wcount, int64_t* bbase, const PairSink& o) {
   const int wave = threadIdx.x / 64;
   if (__lane_id() == 0) wcount[wave] = em.count;
   __syncthreads();
@@ -467,407 +468,537 @@ __device__ __forceinline__ void block_flush(WaveEmitter& em, int* wcount, int64_
   }
 }
 
-// Two lanes per leaf s, depth-first over the subtrees holding leaves after s.  A visited node
-// tests its four children at once (one contiguous load); the pending children of every level
-// on the current path are kept as 4-bit masks in one 64-bit word, so no stack is needed.
-// Block b's 256 queries are exactly the leaves of the level-4 node b.  That subtree (leaf
-// records, leaf boxes and the 84 boxes above them) is staged in LDS; waves 0-3 search it
-// (the local part, LDS only) while waves 4-7 search everything after it from the root (the
-// global part), so each query costs the larger of the two instead of their sum.
-// The top levels of the tree (those that fit kTopCap boxes, never below level 4) are staged
-// in LDS too, so the global part reads only the levels 3..0 of other blocks' subtrees.
-constexpr int kSubLevels = 4;                       // 4^4 = 256 = kBpBlock leaves per block
-constexpr int kSubInner = 64 + 16 + 4;              // boxes of levels 1..3 inside the subtree
-constexpr int kTravThreads = 2 * kBpBlock;          // a local and a global lane per query
-constexpr int kTravWaves = kTravThreads / 64;
-constexpr int kTopCap = 864;                        // 27 KB of top-level boxes
+// ---- the traversal: one wave per group of 64 consecutive leaves ---------------------------
+// Group g holds the leaves [64 g, 64 g + 64) (a level-3 node), which lie close together in
+// Morton order, so one search of the tree serves all of them: the wave pops up to 16 nodes from
+// a stack in LDS, four lanes each load one child's box and test it against the group's box,
+// overlapping inner children go back on the stack, overlapping leaves to a candidate list.
+// Every 64 candidates are then tested against the 64 queries, a candidate per lane, the queries
+// broadcast one after the other; the pairs whose boxes overlap are listed candidate by
+// candidate, and 64 of these at a time take the exact closed box test and the shared-vertex
+// test and are emitted.  On the noisy spheres a group visits about 100 nodes, meets about 120
+// candidates besides its own leaves and keeps about 750 of their 11,000 combinations.
+//
+// Bound by instruction issue (3,300 to 3,600 VALU instructions a group, half of the issue
+// peak) and the latency of the node loads.  With a depth-first search per leaf, whose waves lasted
+// as long as their slowest lane's chain of dependent visits, the two kernels took 4.05 ms on a
+// 4,194,304-triangle sphere of 20.8 M candidates, now 0.97 ms; 0.98 and 0.28 ms on a
+// 1,048,576-triangle sphere of 4.6 M, 97 and 56 us on a 130,050-triangle cloth.  (Persistent waves,
+// two tree levels a step and 32 nodes a step measured no faster, in more registers.)
+//
+// The candidate test runs on 10, 10 and 9 bit integers: a monotone map of the coordinates on
+// the group's box, the same for queries and candidates, so boxes that overlap keep overlapping.
+// The three high ends are packed in one word, with an empty guard bit above each field, and the
+// three low ends in another, each as the guard's value less the end: the sum of the two has a
+// guard bit set iff that high end is not below that low end, so two additions and one and
+// decide the six comparisons of a pair.
+//
+// A pair is reported from the group of its first leaf: candidates are leaves after the group,
+// and within the group those after the query.  A node whose triangles all hold the vertex that
+// all the group's triangles hold is skipped (every pair of the two is adjacent): a fan of thin
+// triangles around a pole would otherwise be tested all against all.
+constexpr int kGroup = 64;
+constexpr int kGroupLevel = 3;       // 4^3 = 64 leaves
+constexpr int kTravWaves = 4;
+constexpr int kTravThreads = 64 * kTravWaves;
+constexpr int kTravMinWaves = 5;     // waves per SIMD that its registers are held to (4: 9% slower, 6: as fast)
+constexpr int kEmitTrav = 512;       // a wave's pair buffer
+constexpr int kSurv = 512;           // a wave's list of overlapping pairs
+constexpr int kStack = 256;
+// 16 nodes are popped while the stack holds at most kStackWide entries, one above that: a
+// 16-node step leaves at most kStackWide + 48, and depth-first steps of one node add at most 3
+// per level to it, 48 in all.
+constexpr int kStackWide = kStack - 48 - 48;
+constexpr uint32_t kGuard = (1u << 10) | (1u << 21) | (1u << 31);
+// The budget (a launch parameter, 128 by default) counts three units for a step of 16 nodes and
+// for 64 pairs tested, about 40 steps in all, where a usual group takes 20: candidates are
+// handed over from there on.  Nodes are only handed over after many more steps, since a part
+// that starts from one node repeats the group's setup for few candidates.  Measured, broad phase
+// of the 4,194,304-triangle sphere at 64, 96, 128, 192: 1.38, 1.25, 1.23, 1.22 ms; of the
+// 1,048,576-triangle one: 0.40, 0.39, 0.41, 0.43 ms.
+constexpr int kNodeBudget = 2;
+// Queries overlapping one candidate from which adjacency is tested before the pairs are listed:
+// 64 more comparisons a batch, which pay where nearly the whole group shares a vertex with it.
+constexpr int kDense = 48;
 
-// A lane that has visited `budget` nodes (a launch parameter, 128 by default) hands the rest
-// of its search to k_traverse_heavy (a wave per query, or per batch of queries when many are
-// deferred), by saving its depth-first state: the node it is about to visit and the pending
-// siblings of every ancestor up to its starting level.  At the default budget few queries get
-// there -- those whose boxes overlap hundreds of others, as in the fan of thin triangles around
-// a pole; a low budget defers many short searches instead.
-struct TravState {
-  int32_t s;      // query leaf (sorted position)
-  int32_t part;   // 1: global part (skips the query's own level-4 subtree)
-  int32_t l, k;   // node about to be visited
-  uint64_t pend;  // pending children per level, 4 bits each
-  int32_t top;    // starting level
-  int32_t last;   // end of the query's problem (leaves)
+// What a wave over its budget hands to k_traverse_heavy: the nodes still to be searched (as 1
+// followed by two bits per level for the path from the root), and batches of 64 candidates
+// still to be tested.  A few groups of a mesh have hundreds of times the usual work -- those
+// of a dense fold or a fan, and those at a jump of the Morton curve -- and would each hold a
+// wave long after the others are done.
+struct TravNode {
+  int32_t group;
+  uint32_t node;
+};
+struct __align__(16) TravBatch {
+  int32_t group, count, pad[2];
+  int32_t leaf[64];
+};
+struct TravHeavy {
+  TravNode* nodes;
+  TravBatch* batches;
+  uint32_t node_cap, batch_cap;
 };
 
-// LDS the traversal of one block works from
+struct TravWave {
+  uint32_t stack[kStack];
+  int32_t cleaf[128];    // candidate leaves
+  uint16_t surv[kSurv];  // overlapping pairs: candidate << 6 | query
+};
+
+// The wave's staged pairs.  All pairs of a wave of k_traverse hold one of its 64 queries, so a
+// pair is staged as the query's lane and the other triangle, 5 bytes; a wave of k_traverse_heavy
+// goes from group to group and stages both triangles.
+struct GroupEmitter {
+  struct Buffer {
+    int32_t tri[kEmitTrav];
+    uint8_t query[kEmitTrav];
+  };
+  Buffer* buf;
+  int32_t qtri;  // the lane's query triangle
+  int count;
+  __device__ __forceinline__ void put(int at, int j, int32_t ta, int32_t tb) {
+    buf->tri[at] = tb;
+    buf->query[at] = (uint8_t)j;
+  }
+  // the pairs to pairs[base ...) (every lane calls)
+  __device__ __forceinline__ void store(int64_t base, const PairSink& o) {
+    for (int i0 = 0; i0 < count; i0 += 64) {
+      const int i = min(i0 + __lane_id(), count - 1);
+      const int32_t b = buf->tri[i], a = __shfl(qtri, buf->query[i]);
+      const int64_t slot = base + i;
+      if (i0 + __lane_id() < count && slot < o.cap) reinterpret_cast<int2*>(o.pairs)[slot] = make_int2(min(a, b), max(a, b));
+    }
+  }
+};
+struct PairEmitter {
+  struct Buffer {
+    int2 pair[kEmitTrav];
+  };
+  Buffer* buf;
+  int32_t qtri;
+  int count;
+  __device__ __forceinline__ void put(int at, int, int32_t ta, int32_t tb) { buf->pair[at] = make_int2(min(ta, tb), max(ta, tb)); }
+  __device__ __forceinline__ void store(int64_t base, const PairSink& o) {
+    for (int i = __lane_id(); i < count; i += 64)
+      if (base + i < o.cap) reinterpret_cast<int2*>(o.pairs)[base + i] = buf->pair[i];
+  }
+};
+
+template <class Emitter>
+__device__ __forceinline__ void emit(Emitter& em, bool want, int j, int32_t ta, int32_t tb, const PairSink& o) {
+  const uint64_t m = __ballot(want);
+  if (!m) return;
+  if (want) em.put(em.count + rank_below(m), j, ta, tb);
+  em.count += __popcll(m);
+  if (em.count > kEmitTrav - 64) {
+    wave_lds_sync();
+    int64_t base = 0;
+    if (__lane_id() == 0) base = sink_reserve(o, (uint32_t)em.count);
+    em.store(__shfl(base, 0), o);
+    wave_lds_sync();
+    em.count = 0;
+  }
+}
+
+template <class Emitter>
 struct TravShared {
-  int2 stage[kTravWaves][kEmitCap];
-  int32_t lm[24], loff[24];  // the level table (node counts and offsets fit 32 bits)
+  TravWave w[kTravWaves];
+  typename Emitter::Buffer stage[kTravWaves];
+  int32_t lm[24];
+  uint32_t loff[24];  // the level table
   int wcount[kTravWaves];
   int64_t bbase;
-  LeafRec sleaf[kBpBlock];
-  Box32 sbox[kBpBlock + kSubInner];  // the block's subtree: level 0 at [0, 256), then 1, 2, 3
-  Box32 stop[kTopCap];               // levels lt..L, in storage order
 };
 
-// The search of one part for the lane's query s.  kGlobal is wave-uniform (waves 0-3 search
-// the block's own subtree, waves 4-7 the rest of the tree), so the sources are fixed: the local
-// part reads only LDS, the global part reads the top levels from LDS and the lower levels and
-// the leaves from global memory.  Tests are written without short-circuit branches and the
-// climb takes the lowest pending bit, so the loop carries little divergence.
-template <bool kGlobal>
-__device__ __forceinline__ void traverse_part(TravShared& sh, int32_t n, int32_t blk, int32_t s, bool active, int lt,
-                                              int32_t tbase, int L, const Box32* __restrict__ boxes,
-                                              const LeafRec* __restrict__ leaves, const int32_t* __restrict__ qend,
-                                              TravState* heavy, int64_t heavy_cap, int budget, bool va, WaveEmitter& em,
-                                              const PairSink& sink, Counters* ctr, int& status) {
-  const int qi = s - blk * kBpBlock;
-  const bool small_tree = L <= kSubLevels;
-  int l = kGlobal || small_tree ? L : kSubLevels;
-  int32_t k = kGlobal || small_tree ? 0 : blk;
-  const int top = l;   // the search ends when nothing is pending at or above this level
-  uint64_t pend = 0;   // pending children of level j's current node at bits [4j, 4j + 4)
-  float q[6] = {0, 0, 0, 0, 0, 0};
-  LeafRec me{};
-  int32_t last = n;    // leaves after s up to the end of the query's problem
-  if (active) {
-    if (qend) last = qend[s];
-    me = sh.sleaf[qi];
-    const Box32 b = sh.sbox[qi];
+// The monotone map of one group's coordinates to small integers.  An axis on which the group
+// has no extent to speak of, or an unbounded one, maps to 0 throughout, so nothing is rejected
+// on it.
+struct TravMap {
+  float lo[3], scale[3];
+  __device__ __forceinline__ void set(const Box32& b) {
+#pragma unroll
     for (int c = 0; c < 3; ++c) {
-      q[c] = b.lo[c];
-      q[3 + c] = b.hi[c];
+      const float e = b.hi[c] - b.lo[c];
+      const bool ok = e >= 1.0e-30f && e <= 3.0e38f;
+      lo[c] = ok ? b.lo[c] : 0.0f;
+      scale[c] = ok ? (c < 2 ? 1023.0f : 511.0f) / e : 0.0f;
     }
   }
-  int visits = 0;
-  bool may_defer = true;  // one attempt: with the list full the lane finishes its own search
-  for (int32_t iter = 0; __ballot(active); ++iter) {
-    if (iter > 2 * n + 64) {  // every node is visited at most once: only corruption gets here
-      status = STATUS_CAPACITY;
-      break;
-    }
-    // over budget: hand the remaining search to a wave of its own (when the list has room)
-    const bool over = active && may_defer && visits >= budget;
-    const uint32_t hs = wave_slot(over, &ctr->n_heavy);
-    if (over) may_defer = false;
-    if (over && (int64_t)hs < heavy_cap) {
-      TravState t;
-      t.s = s;
-      t.part = kGlobal ? 1 : 0;
-      t.l = l;
-      t.k = k;
-      t.pend = pend;
-      t.top = top;
-      t.last = last;
-      heavy[hs] = t;
-      active = false;
-    }
-    ++visits;
-    // children of (l, k): (l - 1, 4k + i), only those holding leaves after s (and, in the
-    // global part, never the block's own subtree) up to the problem's last leaf
-    const int lc = l - 1;
-    const int32_t c0 = 4 * k;
-    uint32_t mask = 0;
-    if (active) {
-      int32_t first = lc > 0 ? (s >> (2 * lc)) : s + 1;
-      if (kGlobal && lc == kSubLevels) first = blk + 1;
-      const int32_t lastc = (last - 1) >> (2 * lc);
-      const int32_t hi = min(lastc, sh.lm[lc] - 1);
-      Box32 cb[4];
-      if (!kGlobal) {
-        const int lb = (lc == 0 ? 0 : (lc == 1 ? kBpBlock : (lc == 2 ? kBpBlock + 64 : kBpBlock + 80)));
-        const int li = c0 - (blk << (2 * (kSubLevels - lc)));
-#pragma unroll
-        for (int i = 0; i < 4; ++i) cb[i] = sh.sbox[lb + li + i];
-      } else if (lc >= lt) {
-        const int ti = sh.loff[lc] - tbase + c0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) cb[i] = sh.stop[ti + i];
-      } else {
-        const Box32* g = boxes + sh.loff[lc] + c0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) cb[i] = g[i];
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int32_t c = c0 + i;
-        const bool ov = (q[0] <= cb[i].hi[0]) & (cb[i].lo[0] <= q[3]) & (q[1] <= cb[i].hi[1]) &
-                        (cb[i].lo[1] <= q[4]) & (q[2] <= cb[i].hi[2]) & (cb[i].lo[2] <= q[5]);
-        mask |= (uint32_t)(ov & (c >= first) & (c <= hi)) << i;
-      }
-    }
-    // leaves: exact FP64 box test and the shared-vertex test
-    uint32_t want = 0;
-    int32_t other[4] = {0, 0, 0, 0};
-    if (active && lc == 0 && mask) {
-      LeafRec o[4];
-      if (!kGlobal) {
-        const int li = c0 - blk * kBpBlock;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = sh.sleaf[li + i];
-      } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = leaves[c0 + i];
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        bool ex = (mask >> i) & 1u;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) ex = ex & (me.lo[c] <= o[i].hi[c]) & (o[i].lo[c] <= me.hi[c]);
-        want |= (uint32_t)(ex & !is_adjacent(me.v, o[i].v, va)) << i;
-        other[i] = o[i].tri;
-      }
-    }
-    if (__ballot(want != 0)) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) em.push((want >> i) & 1u, me.tri, other[i], sink);
-    }
-    if (active) {
-      if (lc == 0) mask = 0;
-      if (mask) {
-        // descend into the first child; the others wait in this level's slot
-        const int i = __builtin_ctz(mask);
-        pend |= (uint64_t)(mask & ~(1u << i)) << (4 * lc);
-        l = lc;
-        k = c0 + i;
-      } else {
-        // resume at the lowest level at or above l with a pending child (slots above the
-        // starting level are never set)
-        const uint64_t rem = l < 16 ? pend >> (4 * l) : 0;
-        if (rem == 0) {
-          active = false;
-        } else {
-          const int b = __builtin_ctzll(rem);
-          const int j = l + (b >> 2);
-          pend &= ~(1ull << (4 * l + b));
-          k = ((k >> (2 * (j - l))) & ~3) + (b & 3);
-          l = j;
-        }
-      }
-    }
+  __device__ __forceinline__ uint32_t one(float v, int c) const {
+    const float top = c < 2 ? 1023.0f : 511.0f;
+    const float q = scale[c] > 0.0f ? (v - lo[c]) * scale[c] : 0.0f;
+    return (uint32_t)fminf(fmaxf(q, 0.0f), top);
   }
+  __device__ __forceinline__ uint32_t hi_word(const Box32& b) const {
+    return one(b.hi[0], 0) | one(b.hi[1], 1) << 11 | one(b.hi[2], 2) << 22;
+  }
+  __device__ __forceinline__ uint32_t lo_word(const Box32& b) const {
+    return kGuard - (one(b.lo[0], 0) | one(b.lo[1], 1) << 11 | one(b.lo[2], 2) << 22);
+  }
+};
+
+__device__ __forceinline__ float size2(const Box32& b) {
+  const float e = (b.hi[0] - b.lo[0]) + (b.hi[1] - b.lo[1]) + (b.hi[2] - b.lo[2]);
+  return e * e;
+}
+
+// Half the margin by which two FP32 boxes must overlap for the FP64 boxes to overlap for
+// certain: each end was rounded outwards by less than 2^-23 of itself (or 2^-149).  NaN, so
+// that nothing is certain, for a box with an end that is huge or not finite.
+__device__ __forceinline__ float box_margin(const Box32& b) {
+  const float m = fabsf(b.lo[0]) + fabsf(b.hi[0]) + fabsf(b.lo[1]) + fabsf(b.hi[1]) + fabsf(b.lo[2]) + fabsf(b.hi[2]);
+  return m < 1.0e30f ? 2.5e-7f * m + 1.0e-37f : __builtin_nanf("");
+}
+
+// The query word of lane (i - r) & 15 of the row, as the operand of an addition.
+template <int r>
+__device__ __forceinline__ uint32_t add_rotated(uint32_t q, uint32_t c) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp(q, r ? 0x120 + r : 0xe4, 0xf, 0xf, true) + c;
+}
+template <int r>
+__device__ __forceinline__ uint32_t one_test(uint32_t qlo, uint32_t qhi, uint32_t clo, uint32_t chi) {
+  return add_rotated<r>(qlo, chi) & add_rotated<r>(qhi, clo) & kGuard;
+}
+// The tests of a lane's candidate against the 16 queries of a row, their verdicts shifted into
+// bits.  Four at a time: the comparisons' results are the carries of four additions, each read
+// at least two instructions after it is written.
+template <int r = 0>
+__device__ __forceinline__ void row_tests(uint32_t& bits, uint32_t qlo, uint32_t qhi, uint32_t clo, uint32_t chi) {
+  const uint32_t t0 = one_test<r>(qlo, qhi, clo, chi), t1 = one_test<r + 1>(qlo, qhi, clo, chi),
+                 t2 = one_test<r + 2>(qlo, qhi, clo, chi), t3 = one_test<r + 3>(qlo, qhi, clo, chi);
+  uint64_t c0, c1, c2, c3;
+  asm("v_cmp_eq_u32 %1, %5, %6\n\t"
+      "v_cmp_eq_u32 %2, %5, %7\n\t"
+      "v_cmp_eq_u32 %3, %5, %8\n\t"
+      "v_cmp_eq_u32 %4, %5, %9\n\t"
+      "v_addc_co_u32 %0, %1, %0, %0, %1\n\t"
+      "v_addc_co_u32 %0, %2, %0, %0, %2\n\t"
+      "v_addc_co_u32 %0, %3, %0, %0, %3\n\t"
+      "v_addc_co_u32 %0, %4, %0, %0, %4"
+      : "+&v"(bits), "=&s"(c0), "=&s"(c1), "=&s"(c2), "=&s"(c3)
+      : "s"(kGuard), "v"(t0), "v"(t1), "v"(t2), "v"(t3));
+  if constexpr (r < 12) row_tests<r + 4>(bits, qlo, qhi, clo, chi);
 }
 
 // kVA: pairs sharing exactly one vertex are candidates (a template argument, so the default
-// keeps the plain shared-vertex test in its leaf loop)
-template <bool kVA>
-__global__ void __launch_bounds__(kTravThreads) k_traverse(int64_t n64, Levels lv, const Box32* __restrict__ boxes,
-                                                           const LeafRec* __restrict__ leaves,
-                                                           const int32_t* __restrict__ qend, TravState* heavy,
-                                                           int64_t heavy_cap, int budget, int32_t* pairs,
-                                                           int64_t cap,
-                                                           unsigned long long* npairs, Counters* ctr) {
-  __shared__ TravShared sh;
-  const PairSink sink{pairs, cap, npairs, &ctr->status};
-  const int32_t n = (int32_t)n64;
-  const int32_t blk = (int32_t)xcd_block(blockIdx.x, gridDim.x);
-  const int lt = lv.lt;
-  const int32_t tbase = lt <= lv.L ? (int32_t)lv.off[lt] : 0;
-  const int ntop = lt <= lv.L ? (int)(lv.off[lv.L] + 4 - tbase) : 0;  // through the padded root level
-  for (int i = threadIdx.x; i < ntop; i += kTravThreads) sh.stop[i] = boxes[tbase + i];
-  const int qi = threadIdx.x % kBpBlock;  // query within the block
-  const bool global_part = __builtin_amdgcn_readfirstlane(threadIdx.x) >= kBpBlock;  // wave-uniform
+// keeps the plain shared-vertex test).  kHeavy: the rest of a search handed over by another
+// wave: from the node `start`, or the tests of `batch`.
+template <bool kVA, bool kHeavy, class Emitter>
+__device__ __forceinline__ void search_group(TravWave& sh, const int32_t* lm, const uint32_t* loff, int32_t n, int L,
+                                             int32_t g, uint32_t start, const TravBatch* batch,
+                                             const Box32* __restrict__ boxes,
+                                             const LeafIds* __restrict__ leaves, const double* __restrict__ tbox,
+                                             const int32_t* __restrict__ qend, const TravHeavy& heavy, int budget,
+                                             Emitter& em, const PairSink& sink,
+                                             Counters* ctr) {
+  const int lane = __lane_id();
+  const int32_t s0 = g * kGroup;
+  const int nq = min(kGroup, n - s0);
+  // the group's box and the queries' (lanes past the last leaf repeat it, and are masked out)
+  const Box32 gb = L >= kGroupLevel ? boxes[loff[kGroupLevel] + (uint32_t)g] : boxes[loff[L]];
+  const int32_t gcom = kVA ? kNoCommon : box_common(gb);
+  const Box32 qb = boxes[(uint32_t)s0 + min(lane, nq - 1)];
+  const LeafIds ql = leaves[s0 + min(lane, nq - 1)];
+  TravMap map;
+  map.set(gb);
+  // (a lane past the last leaf gets a low word that sets no guard)
+  const uint32_t qlo = lane < nq ? map.lo_word(qb) : 0u, qhi = map.hi_word(qb);
+  em.qtri = ql.tri;
+  const float qeps = box_margin(qb);
+  // leaves up to the end of the problem of the group's last leaf
+  const int32_t last = qend ? qend[s0 + nq - 1] : n;
+  int nc = 0;          // candidates (uniform)
+  int work = 0, steps = 0;  // steps of 16 nodes and of 64 pairs, three units each; steps of 16 nodes
+
+  // The queries that a lane's box (clo, chi) overlaps, as bits.  The queries of row R (16 lanes)
+  // come to the lanes of row R ^ v by one exchange, and to every lane of the row by 16 rotations,
+  // which the additions take as their operand's lane pattern: at (v, r), bit
+  // 31 - (16 (v & 1) + r) of word v >> 1, lane 16 R + i meets query 16 (R ^ v) + ((i - r) & 15).
+  const int row = lane >> 4, li = lane & 15;
+  const auto overlaps = [&](uint32_t clo, uint32_t chi, uint32_t (&m)[2]) {
+    m[0] = m[1] = 0u;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const uint32_t vlo = v ? __shfl_xor(qlo, 16 * v) : qlo, vhi = v ? __shfl_xor(qhi, 16 * v) : qhi;
+      row_tests(m[v >> 1], vlo, vhi, clo, chi);
+    }
+  };
+  // tests cnt <= 64 candidates, a lane each (box cb, ids cl, packed box clo, chi), against the
+  // queries; own: the candidates are the queries, each paired with those before it
+  const auto settle = [&](int cnt, bool own, int32_t leaf, const Box32& cb, const LeafIds& cl, uint32_t clo,
+                          uint32_t chi) {
+    uint32_t m[2];
+    overlaps(clo, chi, m);
+    // lanes past the last candidate, and a query's own leaf and those before it, do not count
+    if (lane >= cnt) m[0] = m[1] = 0u;
+    if (own) {
+      const auto before = [&](int v) { return (row ^ v) < row ? 0xffffu : 0u; };
+      // in the own row, ((i - r) & 15) < i iff 1 <= r <= i
+      m[0] &= (0x7fffu & ~(0x7fffu >> li)) << 16 | before(1);
+      m[1] &= before(2) << 16 | before(3);
+    }
+    int p = __popc(m[0]) + __popc(m[1]);
+    if (!kVA && __ballot(p >= kDense)) {
+      // many queries at once (a fan, a fold): most of them share a vertex with the candidate
+#pragma unroll 4
+      for (int j = 0; j < 64; ++j) {
+        const int32_t v[3] = {__builtin_amdgcn_readlane(ql.v[0], j), __builtin_amdgcn_readlane(ql.v[1], j),
+                              __builtin_amdgcn_readlane(ql.v[2], j)};
+        const int jv = (j >> 4) ^ row;
+        const uint32_t clear = is_adjacent(v, cl.v, false) ? 0x80000000u >> (16 * (jv & 1) + ((li - j) & 15)) : 0u;
+        if (jv < 2) m[0] &= ~clear;
+        else m[1] &= ~clear;
+      }
+      p = __popc(m[0]) + __popc(m[1]);
+    }
+    const float ceps = box_margin(cb);
+    // the pairs go through the list kSurv at a time, candidate by candidate
+    const int incl = wave_incl_sum(p);
+    const int total = __builtin_amdgcn_readlane(incl, 63);
+    int at = incl - p;
+    for (int w0 = 0; w0 < total; w0 += kSurv) {
+      const int stop = min(incl, w0 + kSurv), ns = min(total - w0, kSurv);
+      while (at < stop) {
+        const int w = m[0] ? 0 : 1;
+        const int b = __builtin_clz(w ? m[1] : m[0]);
+        const uint32_t bit = 0x80000000u >> b;
+        if (w) m[1] ^= bit;
+        else m[0] ^= bit;
+        const int j = ((row ^ (2 * w + (b >> 4))) << 4) | ((li - b) & 15);
+        sh.surv[at - w0] = (uint16_t)(lane << 6 | j);
+        ++at;
+      }
+      wave_lds_sync();
+      work += 3 * ((ns + 63) >> 6);
+      for (int b0 = 0; b0 < ns; b0 += 64) {
+        bool want = b0 + lane < ns;
+        const int it = want ? sh.surv[b0 + lane] : 0;
+        const int k = it >> 6, j = it & 63;
+        float d = __shfl(cb.hi[0], k) - __shfl(qb.lo[0], j);
+        d = fminf(d, __shfl(qb.hi[0], j) - __shfl(cb.lo[0], k));
+        d = fminf(d, __shfl(cb.hi[1], k) - __shfl(qb.lo[1], j));
+        d = fminf(d, __shfl(qb.hi[1], j) - __shfl(cb.lo[1], k));
+        d = fminf(d, __shfl(cb.hi[2], k) - __shfl(qb.lo[2], j));
+        d = fminf(d, __shfl(qb.hi[2], j) - __shfl(cb.lo[2], k));
+        const float eps = __shfl(ceps, k) + __shfl(qeps, j);
+        const int32_t av[3] = {__shfl(ql.v[0], j), __shfl(ql.v[1], j), __shfl(ql.v[2], j)};
+        const int32_t bv[3] = {__shfl(cl.v[0], k), __shfl(cl.v[1], k), __shfl(cl.v[2], k)};
+        const int32_t ta = __shfl(ql.tri, j), tb = __shfl(cl.tri, k);
+        const int32_t lb = __shfl(leaf, k);
+        want = want && !(d < 0.0f) && !is_adjacent(av, bv, kVA);
+        if (qend) want = want && lb < qend[s0 + j];  // a group over the end of a problem
+        if (want && !(d >= eps)) {
+          // within the rounding of the FP32 boxes: the FP64 ones decide
+          const double* A = tbox + 6 * (int64_t)ta;
+          const double* B = tbox + 6 * (int64_t)tb;
+#pragma unroll
+          for (int c = 0; c < 3; ++c) want = want & (A[c] <= B[3 + c]) & (B[c] <= A[3 + c]);
+        }
+        emit(em, want, j, ta, tb, sink);
+      }
+      wave_lds_sync();  // the list is written again
+    }
+  };
+  // A group is loosely packed when its box is much larger than what its quads of leaves (or,
+  // of a quad that is itself loose, its leaves) cover: at a jump of the Morton curve, or around
+  // one large triangle.  Its search then tests the queries' boxes too, so that it does not meet
+  // everything between them.
+  bool loose = false;
+  if (!kHeavy || !batch) {
+    const float s1 = lane < nq ? size2(qb) : 0.0f;
+    Box32 quad = qb;
+    float s4 = s1;
+#pragma unroll
+    for (int d = 1; d < 4; d <<= 1) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        quad.lo[c] = fminf(quad.lo[c], __shfl_xor(quad.lo[c], d));
+        quad.hi[c] = fmaxf(quad.hi[c], __shfl_xor(quad.hi[c], d));
+      }
+      s4 += __shfl_xor(s4, d);
+    }
+    const float sq = size2(quad);
+    float tot = sq > 4.0f * s4 ? s1 : ((lane & 3) == 0 && lane < nq ? sq : 0.0f);
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) tot += __shfl_xor(tot, d);
+    loose = size2(gb) > 4.0f * tot;
+  }
+  const auto meets = [](const Box32& a, const Box32& b) {
+    return (a.lo[0] <= b.hi[0]) & (b.lo[0] <= a.hi[0]) & (a.lo[1] <= b.hi[1]) & (b.lo[1] <= a.hi[1]) &
+           (a.lo[2] <= b.hi[2]) & (b.lo[2] <= a.hi[2]);
+  };
+  // whether node (l, c) can hold a candidate
+  Box32 b{};
+  const auto meets_group = [&](int l, int32_t c) {
+    b = boxes[loff[l] + (uint32_t)c];
+    bool ov = meets(gb, b) && !(gcom >= 0 && l > 0 && box_common(b) == gcom);
+    return ov;
+  };
+  // the first node of level l that may hold leaves after the group
+  const auto first_node = [&](int l) {
+    return l > kGroupLevel ? g >> (2 * (l - kGroupLevel)) : (g + 1) << (2 * (kGroupLevel - l));
+  };
+
+  int sp = 0;
+  if (kHeavy) {
+    if (batch) {
+      nc = batch->count;
+      if (lane < nc) sh.cleaf[lane] = batch->leaf[lane];
+    } else {
+      if (lane == 0) sh.stack[0] = start;
+      sp = 1;
+    }
+  } else {
+    // start at the lowest level of at most 64 nodes, a lane each
+    int ls = L;
+    while (ls > 0 && lm[ls - 1] <= 64) --ls;
+    if (ls > 0) {
+      const bool ov = lane < lm[ls] && lane >= first_node(ls) && lane <= (last - 1) >> (2 * ls) && meets_group(ls, lane);
+      const uint64_t m = __ballot(ov);
+      if (ov) sh.stack[rank_below(m)] = (1u << (2 * (L - ls))) + (uint32_t)lane;
+      sp = __popcll(m);
+    }
+  }
+  wave_lds_sync();
+  bool may_defer = !kHeavy;
+  // the group's own leaves are the first candidates, then those the search finds, 64 at a time
+  for (bool own = !kHeavy;; own = false) {
+    while (!own && nc < 64 && sp > 0) {
+      if (may_defer && steps > kNodeBudget * budget) {
+        // the nodes still to be searched, as far as the list has room
+        uint32_t base = 0;
+        if (lane == 0) base = atomicAdd(&ctr->n_heavy, (uint32_t)sp);
+        base = __shfl(base, 0);
+        const int fit = base < heavy.node_cap ? (int)min((uint32_t)sp, heavy.node_cap - base) : 0;
+        for (int i = lane; i < fit; i += 64) heavy.nodes[base + i] = TravNode{g, sh.stack[sp - 1 - i]};
+        sp -= fit;
+        may_defer = false;
+        if (sp == 0) break;
+      }
+      work += 3;
+      ++steps;
+      const int take = sp <= kStackWide ? min(sp, 16) : 1;
+      const int t = lane >> 2;
+      const bool act = t < take;
+      const uint32_t code = act ? sh.stack[sp - 1 - t] : 1u;
+      sp -= take;
+      wave_lds_sync();
+      const int depth = (31 - __builtin_clz(code)) >> 1;
+      const int lc = max(L - depth - 1, 0);
+      const int32_t c = (int32_t)(4u * (code - (1u << (2 * depth))) + (uint32_t)(lane & 3));
+      bool ov = act && c >= first_node(lc) && c <= (last - 1) >> (2 * lc) && c < lm[lc] && meets_group(lc, c);
+      if (loose && __ballot(ov)) {
+        uint32_t m[2];
+        overlaps(map.lo_word(b), map.hi_word(b), m);
+        ov = ov && (m[0] | m[1]);
+      }
+      const uint64_t inner = __ballot(ov && lc > 0), leaf = __ballot(ov && lc == 0);
+      if (ov && lc > 0) sh.stack[sp + rank_below(inner)] = 4u * code + (uint32_t)(lane & 3);
+      sp += __popcll(inner);
+      if (ov && lc == 0) sh.cleaf[nc + rank_below(leaf)] = c;
+      nc += __popcll(leaf);
+      wave_lds_sync();
+    }
+    const int cnt = own ? nq : min(nc, 64);
+    if (cnt == 0) break;
+    bool handed = false;
+    if (!kHeavy && !own && work > budget) {  // over the budget: left to another wave, if the list has room
+      uint32_t at = 0;
+      if (lane == 0) at = atomicAdd(&ctr->n_batches, 1u);
+      at = __shfl(at, 0);
+      if (at < heavy.batch_cap) {
+        if (lane == 0) {
+          heavy.batches[at].group = g;
+          heavy.batches[at].count = cnt;
+        }
+        if (lane < cnt) heavy.batches[at].leaf[lane] = sh.cleaf[lane];
+        handed = true;
+      }
+    }
+    if (!handed) {
+      const int32_t leaf = own ? s0 + min(lane, nq - 1) : sh.cleaf[lane < cnt ? lane : 0];
+      const Box32 cb = boxes[(uint32_t)leaf];
+      const LeafIds cl = leaves[leaf];
+      settle(cnt, own, leaf, cb, cl, map.lo_word(cb), map.hi_word(cb));
+    }
+    if (!own) {  // the rest of the list moves to its start
+      nc -= cnt;
+      const int32_t rest = sh.cleaf[64 + lane];
+      wave_lds_sync();
+      if (lane < nc) sh.cleaf[lane] = rest;
+      wave_lds_sync();
+    }
+  }
+}
+
+template <class Shared>
+__device__ __forceinline__ void level_table(Shared& sh, const Levels& lv) {
   if (threadIdx.x < 24) {
     sh.lm[threadIdx.x] = (int32_t)lv.m[threadIdx.x];
-    sh.loff[threadIdx.x] = (int32_t)lv.off[threadIdx.x];
-  }
-  // stage the block's subtree
-  const int32_t s = blk * kBpBlock + qi;
-  if (!global_part && s < n) {
-    sh.sleaf[qi] = leaves[s];
-    sh.sbox[qi] = boxes[s];
-  }
-  if (global_part) {
-    const int t = qi;
-    int l = 0, local = 0, base = kBpBlock;  // thread t < 84 loads inner box t
-    if (t < 64) { l = 1; local = t; base = kBpBlock; }
-    else if (t < 80) { l = 2; local = t - 64; base = kBpBlock + 64; }
-    else if (t < 84) { l = 3; local = t - 80; base = kBpBlock + 80; }
-    if (l > 0 && l <= lv.L) {
-      const int64_t k = ((int64_t)blk << (2 * (kSubLevels - l))) + local;
-      if (k < lv.m[l]) sh.sbox[base + local] = boxes[lv.off[l] + k];
-    }
+    sh.loff[threadIdx.x] = (uint32_t)lv.off[threadIdx.x];
   }
   __syncthreads();
-
-  WaveEmitter em{sh.stage[threadIdx.x / 64], 0};
-  int status = 0;
-  const bool small_tree = lv.L <= kSubLevels;
-  if (global_part)
-    traverse_part<true>(sh, n, blk, s, s < n && !small_tree, lt, tbase, lv.L, boxes, leaves, qend, heavy, heavy_cap,
-                        budget, kVA, em, sink, ctr, status);
-  else
-    traverse_part<false>(sh, n, blk, s, s < n, lt, tbase, lv.L, boxes, leaves, qend, heavy, heavy_cap, budget, kVA,
-                         em, sink, ctr, status);
-  block_flush<kTravWaves>(em, sh.wcount, &sh.bbase, sink);
-  if (status) atomicCAS(&ctr->status, 0, status);
 }
 
-// One wave per batch of saved queries (one query while the list is no longer than the grid,
-// at most kHeavyQ), skipping every subtree whose triangles all hold one of the query's
-// vertices: the remaining nodes of all of them form
-// one stack in LDS, each entry tagged with its query's slot; every step each lane takes one
-// node, tests its four children against that query's box, and pushes the overlapping inner
-// children (or tests the leaves).  A query that overlaps hundreds of leaves needs tens of steps
-// instead of hundreds of serial visits, and queries with a few visits left share the wave's
-// lanes instead of holding a whole wave each.  Everything but the stack is read from global
-// memory.
-//
-// Stack bound: a query saved at level l brings at most 1 + 3 (L - l) entries, and a step
-// replaces at most 64 entries by at most 256 children one level down, so the stack holds at
-// most Q (1 + 3 L) + 3 * 64 * L + 64 entries; the host picks Q so that this fits kHeavyStack.
-constexpr int kHeavyStack = 4096;
-constexpr int kHeavyQ = 32;
-
-inline int heavy_batch(int L) {
-  const int q = (kHeavyStack - 64 - 3 * 64 * L) / (1 + 3 * L);
-  return q < 1 ? 1 : (q > kHeavyQ ? kHeavyQ : q);
-}
-
-__global__ void __launch_bounds__(64) k_traverse_heavy(Levels lv, const Box32* __restrict__ boxes,
-                                                       const LeafRec* __restrict__ leaves,
-                                                       const TravState* __restrict__ heavy, int64_t heavy_cap, int va,
-                                                       int nq_max, int32_t* pairs, int64_t cap,
-                                                       unsigned long long* npairs, Counters* ctr) {
-  const PairSink sink{pairs, cap, npairs, &ctr->status};
-  __shared__ int2 stack[kHeavyStack];  // (level | slot << 8, node)
-  __shared__ int2 stage[kEmitCap];
-  __shared__ int wcount[1];
-  __shared__ int64_t bbase;
-  __shared__ float sq[kHeavyQ][6];      // per slot: the query's FP32 box
-  __shared__ LeafRec sme[kHeavyQ];      // its leaf record
-  __shared__ int32_t ss[kHeavyQ], slast[kHeavyQ], spart[kHeavyQ];
-  WaveEmitter em{stage, 0};
-  const int lane = __lane_id();
-  int status = 0;
-  const int64_t nh = min((int64_t)ctr->n_heavy, heavy_cap);
-  // one query per wave while the list is no longer than the grid, then batches just large
-  // enough to cover it in one pass (at most nq_max)
-  const int per = (int)min((int64_t)nq_max, max((int64_t)1, (nh + gridDim.x - 1) / gridDim.x));
-  for (int64_t it0 = (int64_t)blockIdx.x * per; it0 < nh; it0 += (int64_t)gridDim.x * per) {
-    const int nq = (int)min((int64_t)per, nh - it0);
-    // lane j < nq loads query j and lists its remaining search: the node it was about to
-    // visit and the pending siblings of its ancestors (slot j of pend: siblings at level j)
-    TravState t{};
-    int cnt = 0;
-    if (lane < nq) {
-      t = heavy[it0 + lane];
-      const Box32 qb = boxes[lv.off[0] + t.s];
-      for (int c = 0; c < 3; ++c) {
-        sq[lane][c] = qb.lo[c];
-        sq[lane][3 + c] = qb.hi[c];
-      }
-      sme[lane] = leaves[t.s];
-      ss[lane] = t.s;
-      slast[lane] = t.last;
-      spart[lane] = t.part;
-      cnt = 1;
-      for (int j = t.l; j < t.top; ++j) cnt += __popc((uint32_t)(t.pend >> (4 * j)) & 15u);
-    }
-    int incl = cnt;
-    for (int d = 1; d < 64; d <<= 1) {
-      const int y = __shfl_up(incl, d);
-      if (lane >= d) incl += y;
-    }
-    int sp = __shfl(incl, 63);
-    if (sp > kHeavyStack) {  // excluded by the host's choice of nq_max; never silent
-      status = STATUS_CAPACITY;
-      break;
-    }
-    if (lane < nq) {
-      int pos = incl - cnt;
-      stack[pos++] = make_int2(t.l | lane << 8, t.k);
-      for (int j = t.l; j < t.top; ++j) {
-        const uint32_t pm = (uint32_t)(t.pend >> (4 * j)) & 15u;
-        const int32_t anc = t.k >> (2 * (j - t.l));
-        for (int i = 0; i < 4; ++i)
-          if (pm & (1u << i)) stack[pos++] = make_int2(j | lane << 8, (anc & ~3) + i);
-      }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    while (sp > 0) {
-      const int take = sp < 64 ? sp : 64;
-      int2 node = make_int2(0, 0);
-      const bool act = lane < take;
-      if (act) node = stack[sp - 1 - lane];
-      sp -= take;
-      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      const int slot = node.x >> 8;
-      const int lc = (node.x & 255) - 1;
-      const int64_t c0 = 4 * (int64_t)node.y;
-      const int64_t s = ss[slot];
-      uint32_t mask = 0;
-      if (act) {
-        float q[6];
-        for (int c = 0; c < 6; ++c) q[c] = sq[slot][c];
-        int64_t first = lc > 0 ? (s >> (2 * lc)) : s + 1;
-        if (spart[slot] != 0 && lc == kSubLevels) first = s / kBpBlock + 1;
-        const int64_t lastc = ((int64_t)slast[slot] - 1) >> (2 * lc);
-        const int64_t mcount = lv.m[lc];
-        const Box32* g = boxes + lv.off[lc] + c0;
-        Box32 cb[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) cb[i] = g[i];
-        const int32_t* qv = sme[slot].v;
-        const int32_t qv3[3] = {qv[0], qv[1], qv[2]};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int64_t c = c0 + i;
-          if (c < mcount && c >= first && c <= lastc && overlap32(q, cb[i]) &&
-              !(lc > 0 && skip_common(cb[i], qv3, va != 0)))
-            mask |= 1u << i;
-        }
-      }
-      // leaves: exact tests and emission
-      bool want[4] = {false, false, false, false};
-      int32_t other[4] = {0, 0, 0, 0};
-      int32_t mine = 0;
-      if (act && lc == 0 && mask) {
-        const LeafRec me = sme[slot];
-        mine = me.tri;
-        LeafRec o[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = leaves[c0 + i];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          bool exact = (mask >> i) & 1u;
-          for (int c = 0; c < 3; ++c) exact = exact && me.lo[c] <= o[i].hi[c] && o[i].lo[c] <= me.hi[c];
-          want[i] = exact && !is_adjacent(me.v, o[i].v, va);
-          other[i] = o[i].tri;
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) em.push(want[i], mine, other[i], sink);
-      // inner children: onto the stack (wave prefix sum of the counts), with the slot tag
-      const int ccnt = act && lc > 0 ? __popc(mask) : 0;
-      int cincl = ccnt;
-      for (int d = 1; d < 64; d <<= 1) {
-        const int y = __shfl_up(cincl, d);
-        if (lane >= d) cincl += y;
-      }
-      const int total = __shfl(cincl, 63);
-      if (sp + total > kHeavyStack) {
-        status = STATUS_CAPACITY;  // excluded by the bound above; never silent
-        break;
-      }
-      int pos = sp + cincl - ccnt;
-      for (int i = 0; i < 4; ++i)
-        if (ccnt && (mask & (1u << i))) stack[pos++] = make_int2(lc | slot << 8, (int32_t)(c0 + i));
-      sp += total;
-      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-    }
-    if (status) break;
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();  // the slot arrays are refilled by the next batch
+// End of a block: one atomic reserves the space of all its waves.
+template <class Emitter, class Shared>
+__device__ __forceinline__ void end_emit(Emitter& em, Shared& sh, const PairSink& o) {
+  const int wave = threadIdx.x / 64;
+  if (__lane_id() == 0) sh.wcount[wave] = em.count;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t tot = 0;
+    for (int w = 0; w < kTravWaves; ++w) tot += sh.wcount[w];
+    sh.bbase = tot ? sink_reserve(o, tot) : 0;
   }
-  block_flush<1>(em, wcount, &bbase, sink);
-  if (status) atomicCAS(&ctr->status, 0, status);
+  __syncthreads();
+  int64_t base = sh.bbase;
+  for (int w = 0; w < wave; ++w) base += sh.wcount[w];
+  em.store(base, o);
 }
 
-// number of set bits of m below this lane
-__device__ __forceinline__ int rank_below(uint64_t m) {
-  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+template <bool kVA>
+__global__ void __launch_bounds__(kTravThreads, kTravMinWaves) k_traverse(int64_t n64, Levels lv, const Box32* __restrict__ boxes,
+                                                           const LeafIds* __restrict__ leaves,
+                                                           const double* __restrict__ tbox,
+                                                           const int32_t* __restrict__ qend, TravHeavy heavy, int budget,
+                                                           int32_t* pairs, int64_t cap, unsigned long long* npairs,
+                                                           Counters* ctr) {
+  __shared__ TravShared<GroupEmitter> sh;
+  const PairSink sink{pairs, cap, npairs, &ctr->status};
+  level_table(sh, lv);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const int64_t g = xcd_block(blockIdx.x, gridDim.x) * kTravWaves + wave;
+  GroupEmitter em{&sh.stage[wave], 0, 0};
+  if (g * kGroup < n64)
+    search_group<kVA, false>(sh.w[wave], sh.lm, sh.loff, (int32_t)n64, lv.L, (int32_t)g, 0u, nullptr, boxes, leaves,
+                             tbox, qend, heavy, budget, em, sink, ctr);
+  end_emit(em, sh, sink);
+}
+
+// What the waves over their budget handed over, a wave per batch or node.
+template <bool kVA>
+__global__ void __launch_bounds__(kTravThreads, kTravMinWaves) k_traverse_heavy(int64_t n64, Levels lv, const Box32* __restrict__ boxes,
+                                                                 const LeafIds* __restrict__ leaves,
+                                                                 const double* __restrict__ tbox,
+                                                                 const int32_t* __restrict__ qend, TravHeavy heavy,
+                                                                 int32_t* pairs, int64_t cap,
+                                                                 unsigned long long* npairs, Counters* ctr) {
+  __shared__ TravShared<PairEmitter> sh;
+  const PairSink sink{pairs, cap, npairs, &ctr->status};
+  const int64_t nb = min(ctr->n_batches, heavy.batch_cap), nn = min(ctr->n_heavy, heavy.node_cap);
+  if ((int64_t)blockIdx.x * kTravWaves >= nb + nn) return;  // (the whole block)
+  level_table(sh, lv);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  PairEmitter em{&sh.stage[wave], 0, 0};
+  for (int64_t i = (int64_t)blockIdx.x * kTravWaves + wave; i < nb + nn; i += (int64_t)gridDim.x * kTravWaves) {
+    const TravBatch* batch = i < nb ? heavy.batches + i : nullptr;
+    const TravNode node = i < nb ? TravNode{batch->group, 0u} : heavy.nodes[i - nb];
+    search_group<kVA, true>(sh.w[wave], sh.lm, sh.loff, (int32_t)n64, lv.L, node.group, node.node, batch, boxes, leaves,
+                            tbox, qend, heavy, 0, em, sink, ctr);
+  }
+  end_emit(em, sh, sink);
 }
 
 // All i < j without a shared vertex.  A block takes kBruteRows rows i and kBpBlock columns j,
@@ -1139,7 +1270,7 @@ __global__ void __launch_bounds__(kBpBlock) k_hash_pairs(const Counters* ctr, in
   __shared__ int2 stage[kBpBlock / 64][kEmitCap];
   __shared__ int wcount[kBpBlock / 64];
   __shared__ int64_t bbase;
-  WaveEmitter em{stage[threadIdx.x / 64], 0};
+  WaveEmitter<kEmitCap> em{stage[threadIdx.x / 64], 0};
   const int64_t ne = min((int64_t)ctr->n_entries, ecap);
   const HashGrid g = *grid;
   for (int64_t base = (int64_t)blockIdx.x * kBpBlock; base < ne; base += (int64_t)gridDim.x * kBpBlock) {
@@ -1178,7 +1309,7 @@ __global__ void __launch_bounds__(kBpBlock) k_hash_heavy(const Counters* ctr, in
   __shared__ int2 stage[kBpBlock / 64][kEmitCap];
   __shared__ int wcount[kBpBlock / 64];
   __shared__ int64_t bbase;
-  WaveEmitter em{stage[threadIdx.x / 64], 0};
+  WaveEmitter<kEmitCap> em{stage[threadIdx.x / 64], 0};
   const int64_t ne = min((int64_t)ctr->n_entries, ecap);
   const int64_t nh = min((int64_t)ctr->n_heavy, ne);
   const HashGrid g = *grid;
@@ -1221,14 +1352,6 @@ Levels make_levels(int64_t n) {
     m = (m + 3) / 4;
   }
   lv.L = l;
-  // the highest levels whose (padded) boxes fit the traversal's LDS cache, never below level 4
-  int64_t cum = 0;
-  lv.lt = l + 1;
-  for (int k = l; k >= kSubLevels; --k) {
-    if (cum + pad4(lv.m[k]) > kTopCap) break;
-    cum += pad4(lv.m[k]);
-    lv.lt = k;
-  }
   return lv;
 }
 
@@ -1292,7 +1415,7 @@ hipError_t launch_broadphase(Ctx* c, const ttie_mesh* m, int method, const doubl
     int32_t* v1 = wsp<int32_t>(c, L.bvh_vals);
     int32_t* v2 = wsp<int32_t>(c, L.bvh_vals2);
     Box32* boxes = wsp<Box32>(c, L.bvh_boxes);
-    LeafRec* leaves = wsp<LeafRec>(c, L.bvh_leaves);
+    LeafIds* leaves = wsp<LeafIds>(c, L.bvh_leaves);
     int32_t* qend = wsp<int32_t>(c, L.bvh_qend);
     const Levels lv = make_levels(nt);
     stage_begin(c, TTIE_STAGE_BP_BOXES, s);
@@ -1330,21 +1453,22 @@ hipError_t launch_broadphase(Ctx* c, const ttie_mesh* m, int method, const doubl
     }
     stage_end(c, TTIE_STAGE_BP_BUILD, s);
     stage_begin(c, TTIE_STAGE_BP_TRAVERSE, s);
-    // one lane per leaf, block count rounded up to a multiple of the 8 XCDs
-    const int64_t nb = ((nt + kBpBlock - 1) / kBpBlock + 7) / 8 * 8;
-    TravState* heavy = wsp<TravState>(c, L.bvh_heavy);
-    const int64_t heavy_cap = (int64_t)(L.bvh_heavy_bytes / sizeof(TravState));
+    // a wave per 64 leaves, block count rounded up to a multiple of the 8 XCDs
+    const int64_t per = kGroup * kTravWaves;
+    const int64_t nb = ((nt + per - 1) / per + 7) / 8 * 8;
+    // half of the region for the nodes handed over, half for the batches
+    const size_t half = L.bvh_heavy_bytes / 2 / 256 * 256;
+    const TravHeavy heavy{wsp<TravNode>(c, L.bvh_heavy), wsp<TravBatch>(c, L.bvh_heavy + half),
+                          (uint32_t)(half / sizeof(TravNode)), (uint32_t)(half / sizeof(TravBatch))};
     const int budget = (int)ctx_param(c, TTIE_PARAM_TRAV_BUDGET);
-    if (va)
-      k_traverse<true><<<(unsigned)nb, kTravThreads, 0, s>>>(nt, lv, boxes, leaves, tri_off ? qend : nullptr, heavy,
-                                                             heavy_cap, budget, pairs, capacity, npairs, ctr);
-    else
-      k_traverse<false><<<(unsigned)nb, kTravThreads, 0, s>>>(nt, lv, boxes, leaves, tri_off ? qend : nullptr, heavy,
-                                                              heavy_cap, budget, pairs, capacity, npairs, ctr);
+    const int32_t* qe = tri_off ? qend : nullptr;
+    const auto traverse = va ? k_traverse<true> : k_traverse<false>;
+    const auto traverse_heavy = va ? k_traverse_heavy<true> : k_traverse_heavy<false>;
+    traverse<<<(unsigned)nb, kTravThreads, 0, s>>>(nt, lv, boxes, leaves, tbox, qe, heavy, budget, pairs, capacity, npairs,
+                                                   ctr);
     stage_end(c, TTIE_STAGE_BP_TRAVERSE, s);
     stage_begin(c, TTIE_STAGE_BP_HEAVY, s);
-    k_traverse_heavy<<<1024, 64, 0, s>>>(lv, boxes, leaves, heavy, heavy_cap, va, heavy_batch(lv.L), pairs, capacity,
-                                         npairs, ctr);
+    traverse_heavy<<<1024, kTravThreads, 0, s>>>(nt, lv, boxes, leaves, tbox, qe, heavy, pairs, capacity, npairs, ctr);
     stage_end(c, TTIE_STAGE_BP_HEAVY, s);
   }
   return hipGetLastError();

@@ -45,7 +45,7 @@ struct Counters {
   uint32_t last_hits;      // hits of the last completed evaluation (for hvp / get_hits)
   uint64_t n_entries;      // (cell, triangle) entries of the spatial-hash broad phase
   uint32_t n_heavy;        // broad-phase work items handed to a wave-cooperative kernel
-  uint32_t pad_;
+  uint32_t n_batches;      // candidate batches the tree traversal handed over
 };
 
 // Counters of the one-launch scan (tiles taken, tiles done); both are zero between scans.
