@@ -115,7 +115,7 @@ static Layout layout_with(const ttie_limits& lim, size_t scan_bytes, bool eval_o
   L.hash_stri = take_other(E * 4);
   L.touched = take(6 * H * 4);  // the vertex of each row
   L.inc2 = take(6 * H * sizeof(Incidence));
-  L.pcg_vec = take_other(5 * 3 * (size_t)lim.max_verts * 8);
+  L.pcg_vec = take_other(6 * 3 * (size_t)lim.max_verts * 8);
   L.pcg_flag = take_other(V * 4);  // active-row flags, their scan and the active-row list
   L.pcg_pos = take_other(V * 4);
   L.pcg_act = take_other(V * 4);
