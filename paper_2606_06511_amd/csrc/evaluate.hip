@@ -434,8 +434,13 @@ __global__ void __launch_bounds__(kBlock) k_screen_full(const double* __restrict
   if (status) latch(&ctr->status, status);
 }
 
-// exact pass over the deferred candidates
-__global__ void __launch_bounds__(kBlock) k_screen_exact(const double* __restrict__ x, int64_t nv,
+// Exact pass over the deferred candidates (blocks of kExactThreads threads).  On planar and
+// regular surfaces these are a few per cent of the list (nearly coplanar neighbours): with every
+// uncertain sign in fixed point it took 553 us for the 240,000 of a 64-problem batch (3.6 M
+// candidates), bound by the accumulators in scratch memory; with double-word signs, fixed point
+// for what they leave open and for the distances of hits, and the accumulators in shared
+// memory, 104 us.  Two waves fit a SIMD (212 registers), hence the grid of 2048 waves.
+__global__ void __launch_bounds__(kExactThreads) k_screen_exact(const double* __restrict__ x, int64_t nv,
                                                          const int32_t* __restrict__ tris, int64_t nt,
                                                          const int32_t* __restrict__ pairs, int64_t max_pairs,
                                                          double half, int va, HitGeom* __restrict__ hits,
@@ -1450,7 +1455,7 @@ static hipError_t eval_impl(Ctx* c, const ttie_mesh* m, const int32_t* pairs, co
                                   hits, max_hits, defer, full, fsig, nfull, ctr, flags, pair_T);
   stage_end(c, TTIE_STAGE_SCREEN, s);
   stage_begin(c, TTIE_STAGE_SCREEN_EXACT, s);
-  k_screen_exact<<<grid_for(pair_cap, 256), kBlock, 0, s>>>(m->x, nv, m->tris, m->n_tris, pairs, pair_cap, half, va,
+  k_screen_exact<<<4 * grid_for(pair_cap, 512), kExactThreads, 0, s>>>(m->x, nv, m->tris, m->n_tris, pairs, pair_cap, half, va,
                                                             hits, max_hits, defer, ctr, flags, pair_T);
   stage_end(c, TTIE_STAGE_SCREEN_EXACT, s);
   stage_begin(c, TTIE_STAGE_DERIVS, s);

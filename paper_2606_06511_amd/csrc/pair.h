@@ -105,7 +105,9 @@ struct Tri64 {
 };
 
 // exact plane sides of the three vertices of `cut` against the plane of `pl`.  Without
-// kExact a sign the FP64 filter cannot certify returns false (the pair is deferred).
+// kExact a sign the FP64 filter cannot certify returns false (the pair is deferred); with it
+// only the sign of such a vertex is found (its distance is left 0: exact_distances takes it
+// if the pair turns out to intersect).
 template <bool kExact>
 __device__ __forceinline__ bool plane_sides(const Tri64& pl, const Tri64& cut, int s[3], double d[3], int& status) {
   const V3<double> o{pl.p[0][0], pl.p[0][1], pl.p[0][2]};
@@ -125,10 +127,11 @@ __device__ __forceinline__ bool plane_sides(const Tri64& pl, const Tri64& cut, i
       d[k] = 0.0;
     } else {
       if (!kExact) return false;
-      OrientResult r = orient_exact(pl.p[0], pl.p[1], pl.p[2], cut.p[k]);
-      if (r.overflow) status = STATUS_UNSUPPORTED;
-      s[k] = r.sign;
-      d[k] = r.value;
+      int overflow = 0;
+      s[k] = exact_sign(o, V3<double>{pl.p[1][0], pl.p[1][1], pl.p[1][2]}, V3<double>{pl.p[2][0], pl.p[2][1], pl.p[2][2]},
+                        V3<double>{cut.p[k][0], cut.p[k][1], cut.p[k][2]}, overflow);
+      if (overflow) status = STATUS_UNSUPPORTED;
+      d[k] = 0.0;
     }
   }
   return true;
@@ -161,10 +164,10 @@ __device__ __forceinline__ int orient_sign(const V3<double>& p, const V3<double>
   if (fabs(det) > bound) return det > 0 ? 1 : -1;
   if (bound == 0.0) return 0;
   if (!kExact) return 2;
-  const double P[3] = {p.x, p.y, p.z}, Q[3] = {q.x, q.y, q.z}, R[3] = {r.x, r.y, r.z}, S[3] = {s.x, s.y, s.z};
-  OrientResult o = orient_exact(P, Q, R, S);
-  if (o.overflow) status = STATUS_UNSUPPORTED;
-  return o.sign;
+  int overflow = 0;
+  const int sign = exact_sign(p, q, r, s, overflow);
+  if (overflow) status = STATUS_UNSUPPORTED;
+  return sign;
 }
 
 // Sign of the 2D orientation of (a, b, c) with coordinate k dropped; 2 when only the exact path
@@ -383,6 +386,28 @@ __device__ __forceinline__ void interval_ends(const Tri64& A, const Tri64& B, co
   out.kind = PAIR_HIT;
 }
 
+// The distances that plane_sides<true> left open (a sign other than 0 that the FP64 filter does
+// not certify), exactly: of A's vertices against B's plane in da, of B's against A's in db.
+__device__ __forceinline__ void exact_distances(const Tri64& A, const Tri64& B, const int (&sa)[3], const int (&sb)[3],
+                                                double (&da)[3], double (&db)[3]) {
+#pragma unroll 1
+  for (int v = 0; v < 6; ++v) {
+    const bool first = v < 3;
+    const int k = first ? v : v - 3;
+    const Tri64& cut = first ? A : B;
+    const Tri64& pl = first ? B : A;
+    if ((first ? seli(sa, k) : seli(sb, k)) == 0 || (first ? seld(da, k) : seld(db, k)) != 0.0) continue;
+    const V3<double> q = selv(cut, k);
+    const double Q[3] = {q.x, q.y, q.z};
+    const double value = orient_exact(pl.p[0], pl.p[1], pl.p[2], Q).value;
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      if (first && t == k) da[t] = value;
+      if (!first && t == k) db[t] = value;
+    }
+  }
+}
+
 // Full screening of one non-adjacent pair in FP64 with exact decisions.  Without kExact,
 // a pair needing the exact fallback for any sign comes back as PAIR_DEFER.
 template <bool kExact>
@@ -411,7 +436,10 @@ __device__ __forceinline__ Screen screen_pair(const Tri64& A, const Tri64& B, do
   if (!cb.straddle) return out;
   const int x = cuts_intersect<kExact>(A, B, ca, cb, status);
   if (x == 2) out.kind = PAIR_DEFER;
-  if (x == 1) interval_ends(A, B, ca, cb, half, out);
+  if (x == 1) {
+    if (kExact) exact_distances(A, B, sa, sb, out.da, out.db);
+    interval_ends(A, B, ca, cb, half, out);
+  }
   return out;
 }
 

@@ -14,6 +14,12 @@
 // When perm is exactly 0 every monomial has a zero difference factor (a difference of
 // doubles rounds to 0 only when it is 0, and products cannot underflow on the input domain),
 // so the determinant is exactly 0.
+// Signs the filter leaves open are mostly those of nearly coplanar neighbours, whose determinant
+// is the rounding of their coordinates, about 2^-53 of perm.  It is then taken in double-word
+// arithmetic (exact differences, products and sums with the operations analysed by Joldes, Muller and
+// Popescu, ACM TOMS 44(2), 2017): with u = 2^-53 a product is off by at most 7 u^2 of itself and
+// a sum by 3 u^2 of itself, so the determinant is off by at most 23 u^2 perm, and a value above
+// 32 u^2 perm has the exact sign.
 // Otherwise the determinant is recomputed exactly from the 24 signed triple products of the
 // raw coordinates (det[b-a,c-a,p-a] = D(b,c,p) - D(a,b,c) + D(a,b,p) - D(a,c,p) with
 // D(x,y,z) = x.(y x z)) in a two's-complement fixed-point accumulator spanning the exponent
@@ -72,7 +78,11 @@ __device__ __forceinline__ Mant decompose(double x) {
   return r;
 }
 
-// exact determinant sign (and a rounded value) by fixed-point accumulation
+// exact determinant sign (and a rounded value) by fixed-point accumulation.  The accumulator's
+// limbs are addressed at run time; they lie in shared memory, a column per thread, since 24
+// products' carries through scratch memory were nearly all of its time.  Blocks of at most
+// kExactThreads threads only.
+constexpr int kExactThreads = 64;
 __device__ __noinline__ OrientResult orient_exact(const double* a, const double* b, const double* c,
                                                    const double* p) {
   // D(b,c,p) - D(a,b,c) + D(a,b,p) - D(a,c,p); D(x,y,z) = sum over permutations (i,j,k) of
@@ -102,8 +112,12 @@ __device__ __noinline__ OrientResult orient_exact(const double* a, const double*
     r.overflow = 1;
     return r;
   }
-  uint64_t acc[kLimbs];
-  for (int k = 0; k < kLimbs; ++k) acc[k] = 0;
+  __shared__ uint64_t limbs[kLimbs][kExactThreads];
+  struct {
+    uint64_t (*col)[kExactThreads];
+    __device__ __forceinline__ uint64_t& operator[](int k) const { return col[k][threadIdx.x]; }
+  } acc{limbs};
+  for (int k = 0; k < nl; ++k) acc[k] = 0;
 
   for (int t = 0; t < 4; ++t)
     for (int q = 0; q < 6; ++q) {
@@ -182,17 +196,55 @@ __device__ __noinline__ OrientResult orient_exact(const double* a, const double*
   return r;
 }
 
-// Filtered exact orientation of p against the plane (a, b, c).
-__device__ __forceinline__ OrientResult orient(const double* a, const double* b, const double* c, const double* p) {
-  const V3<double> A{a[0], a[1], a[2]};
-  const V3<double> e1 = V3<double>{b[0], b[1], b[2]} - A;
-  const V3<double> e2 = V3<double>{c[0], c[1], c[2]} - A;
-  const V3<double> w = V3<double>{p[0], p[1], p[2]} - A;
-  double det, bound;
-  orient_fp64(e1, e2, w, det, bound);
-  if (fabs(det) > bound) return {det, det > 0 ? 1 : -1, 0, 0};
-  if (bound == 0.0) return {0.0, 0, 0, 0};
-  return orient_exact(a, b, c, p);
+// ---- double-word arithmetic: h + l with |l| <= ulp(h) / 2 ------------------------------------
+struct Dw {
+  double h, l;
+};
+__device__ __forceinline__ Dw two_sum(double a, double b) {
+#pragma clang fp contract(off)
+  const double s = a + b, t = s - a;
+  return {s, (a - (s - t)) + (b - t)};
+}
+__device__ __forceinline__ Dw fast_two_sum(double a, double b) {  // |a| >= |b|
+#pragma clang fp contract(off)
+  const double s = a + b;
+  return {s, b - (s - a)};
+}
+__device__ __forceinline__ Dw dw_add(Dw a, Dw b) {
+#pragma clang fp contract(off)
+  const Dw s = two_sum(a.h, b.h), t = two_sum(a.l, b.l);
+  const Dw v = fast_two_sum(s.h, s.l + t.h);
+  return fast_two_sum(v.h, t.l + v.l);
+}
+__device__ __forceinline__ Dw dw_neg(Dw a) { return {-a.h, -a.l}; }
+__device__ __forceinline__ Dw dw_mul(Dw a, Dw b) {
+#pragma clang fp contract(off)
+  const double p = a.h * b.h;
+  return fast_two_sum(p, fma(a.h, b.l, fma(a.l, b.h, fma(a.h, b.h, -p))));
+}
+
+// Exact sign of det[b - a, c - a, p - a]: in double words, or exactly where that leaves it open.
+// (A call, not inlined: a dozen places need it, rarely.)
+__device__ __noinline__ int exact_sign(V3<double> a, V3<double> b, V3<double> c, V3<double> p, int& overflow) {
+  const auto diff = [](double x, double y) { return two_sum(x, -y); };
+  const Dw e1[3] = {diff(b.x, a.x), diff(b.y, a.y), diff(b.z, a.z)};
+  const Dw e2[3] = {diff(c.x, a.x), diff(c.y, a.y), diff(c.z, a.z)};
+  const Dw w[3] = {diff(p.x, a.x), diff(p.y, a.y), diff(p.z, a.z)};
+  Dw det{0.0, 0.0};
+  double perm = 0.0;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int i = (k + 1) % 3, j = (k + 2) % 3;
+    const Dw m = dw_add(dw_mul(e1[i], e2[j]), dw_neg(dw_mul(e1[j], e2[i])));
+    const Dw t = dw_mul(m, w[k]);
+    det = k == 0 ? t : dw_add(det, t);
+    perm += (fabs(e1[i].h * e2[j].h) + fabs(e1[j].h * e2[i].h)) * fabs(w[k].h);
+  }
+  if (fabs(det.h) > 32.0 * kEps * kEps * perm) return det.h > 0.0 ? 1 : -1;
+  const double A[3] = {a.x, a.y, a.z}, B[3] = {b.x, b.y, b.z}, C[3] = {c.x, c.y, c.z}, P[3] = {p.x, p.y, p.z};
+  const OrientResult r = orient_exact(A, B, C, P);
+  overflow |= r.overflow;
+  return r.sign;
 }
 
 }  // namespace ttie
