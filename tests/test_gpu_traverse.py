@@ -123,3 +123,31 @@ def test_problems_inside_groups():
     got = p[: int(n.item())].cpu().numpy()
     got = got[np.lexsort((got[:, 1], got[:, 0]))]
     assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("n,budget", [(524288, 16), (524288, 0), (524289, 16), (524289, 0)])
+def test_both_handover_rules(n, budget):
+    """On both sides of the size from which searches are handed over later and whole, against the
+    candidates of the spatial hash; a tenth of the triangles in a dense heap, whose searches are
+    over any budget."""
+    import torch
+
+    from paper_2606_06511_amd import ttie
+
+    rng = np.random.default_rng(n)
+    c = rng.uniform(0.0, 100.0, (n, 1, 3))
+    c[: n // 10] = rng.uniform(0.0, 5.0, (n // 10, 1, 3))
+    x = torch.from_numpy((c + rng.normal(0.0, 0.15, (n, 3, 3))).reshape(-1, 3)).cuda()
+    tris = torch.arange(3 * n, dtype=torch.int32, device="cuda").reshape(n, 3)
+    ctx = ttie.Context(0)
+    cap = 4_000_000
+    ctx.reserve(3 * n, n, cap, max_hits=64)
+    ctx.set_param(ttie.PARAM_TRAV_BUDGET, budget)
+    keys = []
+    for method in (ttie.BROAD_HASH, ttie.BROAD_LBVH):
+        p, k = ctx.broadphase(x, tris, method, capacity=cap)
+        assert ctx.status() == ttie.TTIE_OK
+        p = p[: int(k.item())].long()
+        assert len(p) > n // 10
+        keys.append(torch.sort(p[:, 0] * n + p[:, 1]).values)
+    assert torch.equal(*keys)
