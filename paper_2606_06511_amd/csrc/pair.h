@@ -512,10 +512,12 @@ __device__ __forceinline__ void add_endpoint(V3<S> (&out)[6], S sgn, int p, int 
 // are homogeneous of degree 0 in the coordinates, so the scaling changes nothing but the range
 // of the intermediate values, which then neither under- nor overflows in float32.  The plane
 // sides are of degree 3, so the stored ones are scaled by 2^-3e to match.
+// The gradient of one end of the interval: part 0 is a = d(t(P_amin) - t(Q_bmax)), part 1
+// b = d(t(P_amax) - t(Q_bmin)).
 template <class S>
-__device__ __forceinline__ void interval_grads(const V3<S> (&X)[6], const double dstored_a[3],
-                                               const double dstored_b[3], int e, uint32_t desc, double half,
-                                               S a[18], S b[18]) {
+__device__ __forceinline__ void interval_grad(const V3<S> (&X)[6], const double dstored_a[3],
+                                              const double dstored_b[3], int e, uint32_t desc, double half, int part,
+                                              S out[18]) {
   const V3<S> U[3] = {X[0], X[1], X[2]};
   const V3<S> V[3] = {X[3], X[4], X[5]};
   const V3<S> na = cross(U[1] - U[0], U[2] - U[0]);
@@ -530,23 +532,27 @@ __device__ __forceinline__ void interval_grads(const V3<S> (&X)[6], const double
     da[k] = Sc<S>::with_value(dot(nb, U[k] - V[0]), ldexp(dstored_a[k], -3 * e));
     db[k] = Sc<S>::with_value(dot(na, V[k] - U[0]), ldexp(dstored_b[k], -3 * e));
   }
-  V3<S> ga[6], gb[6];
+  V3<S> g[6];
   const S zero = Sc<S>::c(0.0);
 #pragma unroll
-  for (int k = 0; k < 6; ++k) ga[k] = gb[k] = V3<S>{zero, zero, zero};
+  for (int k = 0; k < 6; ++k) g[k] = V3<S>{zero, zero, zero};
   const S pos = Sc<S>::c(half), neg = Sc<S>::c(-half);
-  const int amin = desc_pick(desc, 0), amax = desc_pick(desc, 1);
-  const int bmin = desc_pick(desc, 2), bmax = desc_pick(desc, 3);
-  // a = d(t(P_amin) - t(Q_bmax)), b = d(t(P_amax) - t(Q_bmin))
-  add_endpoint(ga, pos, desc_p(desc, 0, amin), desc_q(desc, 0, amin), U, V, da, nb, Dh, 0, 3);
-  add_endpoint(ga, neg, desc_p(desc, 1, bmax), desc_q(desc, 1, bmax), V, U, db, na, Dh, 3, 0);
-  add_endpoint(gb, pos, desc_p(desc, 0, amax), desc_q(desc, 0, amax), U, V, da, nb, Dh, 0, 3);
-  add_endpoint(gb, neg, desc_p(desc, 1, bmin), desc_q(desc, 1, bmin), V, U, db, na, Dh, 3, 0);
+  const int ea = desc_pick(desc, part), eb = desc_pick(desc, 3 - part);
+  add_endpoint(g, pos, desc_p(desc, 0, ea), desc_q(desc, 0, ea), U, V, da, nb, Dh, 0, 3);
+  add_endpoint(g, neg, desc_p(desc, 1, eb), desc_q(desc, 1, eb), V, U, db, na, Dh, 3, 0);
 #pragma unroll
   for (int k = 0; k < 6; ++k) {
-    a[3 * k] = ga[k].x; a[3 * k + 1] = ga[k].y; a[3 * k + 2] = ga[k].z;
-    b[3 * k] = gb[k].x; b[3 * k + 1] = gb[k].y; b[3 * k + 2] = gb[k].z;
+    out[3 * k] = g[k].x; out[3 * k + 1] = g[k].y; out[3 * k + 2] = g[k].z;
   }
+}
+
+// Both ends.
+template <class S>
+__device__ __forceinline__ void interval_grads(const V3<S> (&X)[6], const double dstored_a[3],
+                                               const double dstored_b[3], int e, uint32_t desc, double half,
+                                               S a[18], S b[18]) {
+  interval_grad<S>(X, dstored_a, dstored_b, e, desc, half, 0, a);
+  interval_grad<S>(X, dstored_a, dstored_b, e, desc, half, 1, b);
 }
 
 // 2x2 core M of the per-pair Hessian J^T M J for each PSD mode (see ttie.h), in FP64.
