@@ -182,7 +182,9 @@ void stage_end(Ctx* c, int stage, hipStream_t s) {
 
 using namespace ttie;
 
-struct ttie_ctx : public Ctx {};
+struct ttie_ctx : public Ctx {
+  std::mutex status_mu;  // one reader of status_pin at a time
+};
 
 namespace {
 
@@ -256,6 +258,18 @@ ttie_status ttie_create(int device, ttie_ctx** out) {
   auto* c = new ttie_ctx();
   std::memset(static_cast<Ctx*>(c), 0, sizeof(Ctx));
   c->device = device;
+  {
+    DeviceGuard g(device);
+    // (a stream that some thread captures meanwhile does not concern this allocation)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    const hipError_t e = hipHostMalloc((void**)&c->status_pin, sizeof(int32_t));
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) {
+      delete c;
+      return hip_fail(e, "ttie_create: host memory of the status");
+    }
+  }
   *out = c;
   g_err.clear();
   return TTIE_OK;
@@ -268,6 +282,10 @@ ttie_status ttie_destroy(ttie_ctx* ctx) {
     if (ctx->timers[k].stop) (void)hipEventDestroy(ctx->timers[k].stop);
   }
   for (int k = 0; k < ctx->n_pool; ++k) (void)hipEventDestroy(ctx->event_pool[k]);
+  {
+    DeviceGuard g(ctx->device);
+    (void)hipHostFree(ctx->status_pin);
+  }
   free(ctx->timers);
   free(ctx->event_pool);
   delete ctx;
@@ -320,12 +338,13 @@ ttie_status ttie_get_status(ttie_ctx* ctx, void* stream, ttie_status* status_hos
   if (!status_host) return fail(TTIE_ERR_INVALID_ARGUMENT, "status_host is NULL");
   DeviceGuard g(ctx->device);
   hipStream_t s = (hipStream_t)stream;
-  int32_t v = 0;
-  hipError_t e = hipStreamSynchronize(s);
-  if (e == hipSuccess) e = hipMemcpy(&v, ctx->ws + ctx->L.counters, sizeof(v), hipMemcpyDeviceToHost);
-  if (e == hipSuccess) e = launch_fill_zero_i32(wsp<int32_t>(ctx, ctx->L.counters), 1, s);
+  // The word is taken and cleared by one kernel that stores it in pinned host memory: one wait,
+  // where a copy and a fill after the stream's end would wait twice more.
+  std::lock_guard<std::mutex> lk(ctx->status_mu);
+  hipError_t e = launch_take_status(wsp<Counters>(ctx, ctx->L.counters), ctx->status_pin, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(e, "ttie_get_status");
+  const int32_t v = *ctx->status_pin;
   *status_host = (ttie_status)v;
   return TTIE_OK;
 }

@@ -39,6 +39,9 @@ constexpr int kWaves = kBlock / 64;
 
 __device__ __forceinline__ void latch(int32_t* status, int code) { atomicCAS(status, 0, code); }
 
+// The latched status to *out (host memory), and cleared.
+__global__ void k_take_status(Counters* ctr, int32_t* out) { *out = atomicExch(&ctr->status, 0); }
+
 __global__ void k_fill_zero_i32(int32_t* p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0;
 }
@@ -1399,6 +1402,11 @@ static unsigned grid_for(int64_t n, unsigned cap = 4096) {
   if (g < 1) g = 1;
   if (g > cap) g = cap;
   return (unsigned)g;
+}
+
+hipError_t launch_take_status(Counters* ctr, int32_t* out, hipStream_t s) {
+  k_take_status<<<1, 1, 0, s>>>(ctr, out);
+  return hipGetLastError();
 }
 
 hipError_t launch_fill_zero_i32(int32_t* p, int64_t n, hipStream_t s) {

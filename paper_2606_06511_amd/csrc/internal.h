@@ -157,6 +157,7 @@ struct Ctx {
   int64_t last_nverts;
   int last_valid;
   int64_t param[TTIE_PARAM_COUNT];  // launch parameters, 0 = default
+  int32_t* status_pin;              // pinned host word that ttie_get_status reads
 };
 
 // a launch parameter of the context (its default when unset)
@@ -176,6 +177,7 @@ void stage_end(Ctx* c, int stage, hipStream_t s);
 
 // launchers (return hipSuccess or the first error)
 hipError_t launch_fill_zero_i32(int32_t* p, int64_t n, hipStream_t s);
+hipError_t launch_take_status(Counters* ctr, int32_t* out, hipStream_t s);
 // n_prob problems own the triangle ranges [tri_off[p], tri_off[p + 1]) (device array; NULL:
 // one problem); no pair joins two problems
 hipError_t launch_broadphase(Ctx* c, const ttie_mesh* m, int method, const double* x_end, int n_prob,
