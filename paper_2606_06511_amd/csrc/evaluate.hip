@@ -3,17 +3,18 @@
 //
 // Pipeline on one stream, no host synchronization:
 //   k_screen         one lane per candidate: adjacency and the FP64-filtered plane sides of both
-//                    triangles; candidates that straddle both ways, and filter-uncertain ones, are
-//                    appended to lists with one atomic per wave (ballot + mbcnt); checks the
-//                    coordinate domain and clears the bitmap of touched vertices
+//                    triangles; candidates that straddle both ways, and filter-uncertain ones
+//                    (marked), go to the wave's own list; checks the coordinate domain and clears
+//                    the bitmap of touched vertices
 //   k_screen_flag    the exact flag of the straddling candidates from their plane sides and four
 //                    orientations; non-hits settled, the rest compacted in the wave's list
 //   k_screen_full    the full screening of what is left (hits, in-plane pairs): segment ends,
-//                    line frame, exact flag, FP64 interval ends; hits appended
+//                    line frame, exact flag, FP64 interval ends; hits appended, and the uncertain
+//                    candidates of the waves' lists gathered in one
 //   k_screen_exact   the uncertain candidates again, with the exact fallback
-//   k_derivs<S>      one lane per hit: a = dt_c^0, b = dt_c^1, T, g (Eq. 3), 2x2 Hessian core;
+//   k_derivs<S>      two lanes per hit: a = dt_c^0, b = dt_c^1, T, g (Eq. 3), 2x2 Hessian core;
 //                    counts the hit's six incidences and marks its vertices in the bitmap
-//   k_rank           one block: per bitmap word, the touched vertices and the incidences below it
+//   k_rank_part, k_rank  per bitmap word, the touched vertices and the incidences below it
 //   k_fill           scatter (pair key, hit, slot) incidences into per-vertex lists; name the rows
 //   k_rank_inc<S>    one thread per incidence: its place in its row in pair-key order (the
 //                    summation order); its hit's vertices as the row's column candidates
@@ -73,13 +74,13 @@ __device__ __forceinline__ uint32_t side_code(const int (&sa)[3], const int (&sb
   return c;
 }
 
+// Returns whether the pair is deferred (never, kExact).
 template <bool kExact>
-__device__ __forceinline__ void screen_one(int64_t p, uint32_t code, const double* __restrict__ x, int64_t nv,
+__device__ __forceinline__ bool screen_one(int64_t p, uint32_t code, const double* __restrict__ x, int64_t nv,
                                            const int32_t* __restrict__ tris, int64_t nt,
                                            const int32_t* __restrict__ pairs, double half, bool va,
-                                           HitGeom* __restrict__ hits, uint32_t max_hits, int32_t* __restrict__ defer,
-                                           int64_t max_defer, Counters* ctr, uint8_t* __restrict__ flags,
-                                           double* __restrict__ pair_T, int& status) {
+                                           HitGeom* __restrict__ hits, uint32_t max_hits, Counters* ctr,
+                                           uint8_t* __restrict__ flags, double* __restrict__ pair_T, int& status) {
   int kind = PAIR_NONE;
   Screen sc;
   sc.t0 = sc.t1 = 0.0;
@@ -119,13 +120,6 @@ __device__ __forceinline__ void screen_one(int64_t p, uint32_t code, const doubl
       }
     }
   }
-  if (!kExact) {
-    const uint32_t ds = wave_slot(kind == PAIR_DEFER, &ctr->n_defer);
-    if (kind == PAIR_DEFER) {
-      if ((int64_t)ds < max_defer) defer[ds] = (int32_t)p;
-      else status = STATUS_CAPACITY;
-    }
-  }
   const bool is_hit = kind == PAIR_HIT;
   const uint32_t slot = wave_slot(is_hit, &ctr->n_hits);
   if (is_hit) {
@@ -146,6 +140,7 @@ __device__ __forceinline__ void screen_one(int64_t p, uint32_t code, const doubl
       status = STATUS_CAPACITY;
     }
   }
+  return !kExact && kind == PAIR_DEFER;
 }
 
 // ---- the fast pass: FP64 filters only, uncertain pairs deferred --------------------------
@@ -159,14 +154,12 @@ __device__ __forceinline__ void screen_one(int64_t p, uint32_t code, const doubl
 // or two lanes.  Every decision and value is exactly the one-pass result.
 enum { STEP_SETTLED = 0, STEP_DEFER = 1, STEP_FULL = 3 };
 
-__device__ __forceinline__ void append(bool want, int64_t p, int32_t* list, int64_t cap, uint32_t* counter,
-                                       int& status) {
-  const uint32_t ds = wave_slot(want, counter);
-  if (want) {
-    if ((int64_t)ds < cap) list[ds] = (int32_t)p;
-    else status = STATUS_CAPACITY;
-  }
-}
+// The code of a listed candidate that is left to the exact pass.  (The deferred ones travel in the
+// lists of the others, at no cost, and k_screen_full gathers them: a reservation for every 64
+// candidates that hold one serialised on the one counter, 57,000 times on a 64-problem batch of
+// 3.6 M candidates, 240,000 of them deferred, where k_screen took 380 us and now 86, k_screen_full
+// 77 instead of 41.)
+constexpr uint32_t kDeferred = 0x8000u;
 
 __device__ __forceinline__ void settle(int64_t p, int kind, uint8_t* flags, double* pair_T) {
   if (flags) flags[p] = (uint8_t)kind;
@@ -244,7 +237,7 @@ __device__ __forceinline__ void wave_chunk(int64_t np, int64_t& beg, int64_t& en
 __global__ void __launch_bounds__(kBlock) k_screen(const double* __restrict__ x, int64_t nv,
                                                    const int32_t* __restrict__ tris, int64_t nt,
                                                    const int32_t* __restrict__ pairs, const int64_t* n_pairs_dev,
-                                                   int64_t max_pairs, int va, int32_t* __restrict__ defer,
+                                                   int64_t max_pairs, int va,
                                                    int32_t* __restrict__ full, uint16_t* __restrict__ fsig,
                                                    int32_t* __restrict__ nfull, Counters* ctr,
                                                    uint8_t* __restrict__ flags,
@@ -266,12 +259,11 @@ __global__ void __launch_bounds__(kBlock) k_screen(const double* __restrict__ x,
       int st = STEP_SETTLED;
       uint32_t code = 0;
       if (p < end) st = screen_stage1(p, x, nv, tris, nt, pairs, va != 0, flags, pair_T, code, status);
-      append(st == STEP_DEFER, p, defer, max_pairs, &ctr->n_defer, status);
-      const uint64_t fm = __ballot(st == STEP_FULL);
-      if (st == STEP_FULL) {
+      const uint64_t fm = __ballot(st != STEP_SETTLED);
+      if (st != STEP_SETTLED) {
         const int64_t at = beg + nf + __popcll(fm & below);
         full[at] = (int32_t)p;
-        fsig[at] = (uint16_t)code;
+        fsig[at] = (uint16_t)(st == STEP_DEFER ? kDeferred : code);
       }
       nf += __popcll(fm);
     }
@@ -297,24 +289,22 @@ __global__ void __launch_bounds__(kBlock) k_screen(const double* __restrict__ x,
 
 // The exact flag of the candidates the first stage passed on with their plane sides, one lane
 // each, on the four orientations only (a small kernel: more waves hide the gathers).  Pairs that
-// do not intersect are settled, the ones whose signs need the exact path go to the deferred
-// list, and the rest -- hits, pairs with a triangle in the other's plane and pairs with a
-// vertex exactly on the other plane -- stay in the wave's list (compacted in place: a batch's
-// writes land below the entries still to be read) for k_screen_full.
+// do not intersect are settled, the ones whose signs need the exact path are marked, and they and
+// the rest -- hits, pairs with a triangle in the other's plane and pairs with a vertex exactly on
+// the other plane -- stay in the wave's list (compacted in place: a batch's writes land below the
+// entries still to be read) for k_screen_full.
 __global__ void __launch_bounds__(kBlock) k_screen_flag(const double* __restrict__ x, int64_t nv,
                                                         const int32_t* __restrict__ tris,
                                                         const int32_t* __restrict__ pairs,
                                                         const int64_t* n_pairs_dev, int64_t max_pairs,
-                                                        int32_t* __restrict__ defer, int32_t* __restrict__ full,
-                                                        uint16_t* __restrict__ fsig, int32_t* __restrict__ nfull,
-                                                        Counters* ctr, uint8_t* __restrict__ flags,
+                                                        int32_t* __restrict__ full, uint16_t* __restrict__ fsig,
+                                                        int32_t* __restrict__ nfull, uint8_t* __restrict__ flags,
                                                         double* __restrict__ pair_T, int64_t tile) {
   const int64_t np = min(*n_pairs_dev, max_pairs);
   int64_t beg, end, wid;
   wave_chunk(np, beg, end, wid);
   const int lane = __lane_id();
   const uint64_t below = (1ull << lane) - 1ull;
-  int status = 0;
   // the wave's units: its chunk, or with the tile queue every nw-th tile from its own id
   const int64_t nw = (int64_t)gridDim.x * kWaves;
   const int64_t units = tile ? (np + tile - 1) / tile : wid + 1;
@@ -326,7 +316,7 @@ __global__ void __launch_bounds__(kBlock) k_screen_flag(const double* __restrict
     const int32_t k = k0 + lane;
     int32_t p = -1;
     uint32_t code = 0;
-    int verdict = 1;  // 0 settled, 1 kept, 2 deferred
+    bool keep = k < nf;
     if (k < nf) {
       p = full[beg + k];
       code = fsig[beg + k];
@@ -338,7 +328,7 @@ __global__ void __launch_bounds__(kBlock) k_screen_flag(const double* __restrict
       }
       // a vertex exactly on the other plane (rare), or a pair without sides (a triangle in
       // the other's plane), is left to k_screen_full's general path
-      if (code && sa[0] && sa[1] && sa[2] && sb[0] && sb[1] && sb[2]) {
+      if (code && code != kDeferred && sa[0] && sa[1] && sa[2] && sb[0] && sb[1] && sb[2]) {
         const LoneCut la = lone_cut(sa[0], sa[1], sa[2]), lb = lone_cut(sb[0], sb[1], sb[2]);
         const int2 ij = reinterpret_cast<const int2*>(pairs)[p];
         const int64_t ta = 3 * (int64_t)ij.x, tb = 3 * (int64_t)ij.y;
@@ -355,12 +345,13 @@ __global__ void __launch_bounds__(kBlock) k_screen_flag(const double* __restrict
         const int sq[2] = {pick(sa[0], sa[1], sa[2], la.q0), pick(sa[0], sa[1], sa[2], la.q1)};
         const int ss[2] = {pick(sb[0], sb[1], sb[2], lb.q0), pick(sb[0], sb[1], sb[2], lb.q1)};
         const int xr = cuts_intersect_lone(P, Q, sq, R, S, ss);
-        verdict = xr == 0 ? 0 : (xr == 2 ? 2 : 1);
-        if (verdict == 0) settle(p, PAIR_NONE, flags, pair_T);
+        if (xr == 2) code = kDeferred;
+        if (xr == 0) {
+          keep = false;
+          settle(p, PAIR_NONE, flags, pair_T);
+        }
       }
     }
-    append(verdict == 2, p, defer, max_pairs, &ctr->n_defer, status);
-    const bool keep = k < nf && verdict == 1;
     const uint64_t km = __ballot(keep);
     if (keep) {
       const int64_t at = beg + kept + __popcll(km & below);
@@ -371,15 +362,16 @@ __global__ void __launch_bounds__(kBlock) k_screen_flag(const double* __restrict
   }
   if (lane == 0) nfull[u] = kept;
   }
-  if (status) latch(&ctr->status, status);
 }
 
 // The full screening (screen_one) of the candidates k_screen_flag kept: few per chunk (the hits,
 // and pairs with a triangle in the other's plane), so each wave takes the lists of kMergeChunks
 // consecutive chunks and screens them 64 at a time (a wave per chunk would pay its chain of
 // dependent loads for one or two pairs).  A pair that straddles both ways comes with its exact
-// plane sides, so the plane distances are computed again for a hit only.
+// plane sides, so the plane distances are computed again for a hit only.  The deferred candidates
+// of the lists and its own it gathers in LDS, and appends to the one list of k_screen_exact.
 constexpr int kMergeChunks = 16;
+constexpr int kLate = 512;        // deferred candidates a wave gathers before it reserves their places
 constexpr int64_t kMaxUnits = 65536 * kWaves;  // entries of nfull: chunks of a 65536-block grid, or tiles
 
 __global__ void __launch_bounds__(kBlock) k_screen_full(const double* __restrict__ x, int64_t nv,
@@ -413,6 +405,23 @@ __global__ void __launch_bounds__(kBlock) k_screen_full(const double* __restrict
   for (int j = 0; j < kMergeChunks; ++j) pre[j] = __shfl(incl, j);
   const int32_t total = pre[kMergeChunks - 1];
   int status = 0;
+  __shared__ int32_t late[kWaves][kLate];  // the waves' deferred candidates
+  int32_t* const mine = late[threadIdx.x / 64];
+  int nl = 0;
+  const auto flush = [&] {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    uint32_t to = 0;
+    if (lane == 0) to = atomicAdd(&ctr->n_defer, (uint32_t)nl);
+    to = __shfl(to, 0);
+    for (int k = lane; k < nl; k += 64) {
+      if ((int64_t)to + k < max_pairs) defer[to + k] = mine[k];
+      else status = STATUS_CAPACITY;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    nl = 0;
+  };
   for (int32_t e0 = 0; e0 < total; e0 += 64) {
     const int32_t e = e0 + lane;
     int64_t p = -1;
@@ -431,9 +440,16 @@ __global__ void __launch_bounds__(kBlock) k_screen_full(const double* __restrict
       p = full[at];
       code = fsig[at];
     }
-    screen_one<false>(p, code, x, nv, tris, nt, pairs, half, va != 0, hits, max_hits, defer, max_pairs, ctr, flags,
-                      pair_T, status);
+    bool put = p >= 0 && code == kDeferred;
+    const bool failed = screen_one<false>(put ? -1 : p, code, x, nv, tris, nt, pairs, half, va != 0, hits, max_hits, ctr,
+                                          flags, pair_T, status);
+    put |= failed;
+    const uint64_t m = __ballot(put);
+    if (put) mine[nl + __popcll(m & ((1ull << lane) - 1ull))] = (int32_t)p;
+    nl += __popcll(m);
+    if (nl > kLate - 64) flush();
   }
+  if (nl) flush();
   if (status) latch(&ctr->status, status);
 }
 
@@ -454,8 +470,8 @@ __global__ void __launch_bounds__(kExactThreads) k_screen_exact(const double* __
   int status = 0;
   for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < nd; base += (int64_t)gridDim.x * blockDim.x) {
     const int64_t q = base + threadIdx.x;
-    screen_one<true>(q < nd ? (int64_t)defer[q] : -1, 0u, x, nv, tris, nt, pairs, half, va != 0, hits, max_hits, nullptr,
-                     0, ctr, flags, pair_T, status);
+    screen_one<true>(q < nd ? (int64_t)defer[q] : -1, 0u, x, nv, tris, nt, pairs, half, va != 0, hits, max_hits, ctr,
+                     flags, pair_T, status);
   }
   if (status) latch(&ctr->status, status);
 }
@@ -1470,10 +1486,10 @@ static hipError_t eval_impl(Ctx* c, const ttie_mesh* m, const int32_t* pairs, co
   // them, the length of nfull)
   int64_t tile = ctx_param(c, TTIE_PARAM_SCREEN_TILE);
   if (tile) tile = std::max<int64_t>(tile, ((pair_cap + kMaxUnits - 1) / kMaxUnits + 63) / 64 * 64);
-  k_screen<<<gscreen, kBlock, 0, s>>>(m->x, nv, m->tris, m->n_tris, pairs, n_pairs, pair_cap, va, defer, full, fsig,
+  k_screen<<<gscreen, kBlock, 0, s>>>(m->x, nv, m->tris, m->n_tris, pairs, n_pairs, pair_cap, va, full, fsig,
                                       nfull, ctr, flags, pair_T, bm, nw, tile);
-  k_screen_flag<<<gscreen, kBlock, 0, s>>>(m->x, nv, m->tris, pairs, n_pairs, pair_cap, defer, full, fsig, nfull, ctr,
-                                           flags, pair_T, tile);
+  k_screen_flag<<<gscreen, kBlock, 0, s>>>(m->x, nv, m->tris, pairs, n_pairs, pair_cap, full, fsig, nfull, flags,
+                                           pair_T, tile);
   const int64_t n_chunks = (int64_t)gscreen * kWaves;
   const int64_t max_units = tile ? (pair_cap + tile - 1) / tile : n_chunks;
   k_screen_full<<<(unsigned)std::max<int64_t>(1, (max_units + kWaves * kMergeChunks - 1) / (kWaves * kMergeChunks)),
