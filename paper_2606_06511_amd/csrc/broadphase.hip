@@ -47,6 +47,26 @@ __global__ void k_bp_init(Counters* c, unsigned long long* npairs) {
   }
 }
 
+// minimum and maximum over the wave's lanes, in lane 63 (the identity comes in where a pattern
+// names no lane)
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint32_t dpp_or(uint32_t v, uint32_t id) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)id, (int)v, kCtrl, kRows, 0xf, false);
+}
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
+  v = min(v, dpp_or<0x111, 0xf>(v, ~0u));
+  v = min(v, dpp_or<0x112, 0xf>(v, ~0u));
+  v = min(v, dpp_or<0x114, 0xf>(v, ~0u));
+  v = min(v, dpp_or<0x118, 0xf>(v, ~0u));
+  v = min(v, dpp_or<0x142, 0xa>(v, ~0u));
+  return min(v, dpp_or<0x143, 0xc>(v, ~0u));
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) { return ~wave_min(~v); }
+
+// A pass over bytes (a triangle's 12 read and its corners' 72, mostly cached; 60 written): 151 us
+// for 4,194,304 triangles, however many threads a block has.  On small meshes its latency counts:
+// with sums through registers instead of shared memory 3.2 us instead of 3.9 on 640 triangles (and
+// k_morton 7.2 instead of 8.0).
 __global__ void __launch_bounds__(kBpBlock) k_tri_boxes(const double* __restrict__ x, const double* __restrict__ x_end,
                                                         int64_t nv, const int32_t* __restrict__ tris, int64_t nt,
                                                         double* __restrict__ tbox, float* __restrict__ centre,
@@ -58,8 +78,9 @@ __global__ void __launch_bounds__(kBpBlock) k_tri_boxes(const double* __restrict
     ctr->n_heavy = 0;
     ctr->n_batches = 0;
   }
-  __shared__ uint32_t smin[3][kBpBlock], smax[3][kBpBlock];
-  __shared__ double sext[kBpBlock];
+  constexpr int kW = kBpBlock / 64;
+  __shared__ uint32_t sb[6][kW];
+  __shared__ double sext[kW];
   uint32_t lmin[3] = {0xffffffffu, 0xffffffffu, 0xffffffffu}, lmax[3] = {0u, 0u, 0u};
   double ext = 0.0;  // sum of the boxes' largest extents (the hash grid's cell size)
   bool bad = false;
@@ -95,9 +116,11 @@ __global__ void __launch_bounds__(kBpBlock) k_tri_boxes(const double* __restrict
       bad = true;
     }
     ext += fmax(hi[0] - lo[0], fmax(hi[1] - lo[1], hi[2] - lo[2]));
+    double2* const row = reinterpret_cast<double2*>(tbox + 6 * t);
+    row[0] = make_double2(lo[0], lo[1]);
+    row[1] = make_double2(lo[2], hi[0]);
+    row[2] = make_double2(hi[1], hi[2]);
     for (int c = 0; c < 3; ++c) {
-      tbox[6 * t + c] = lo[c];
-      tbox[6 * t + 3 + c] = hi[c];
       const uint32_t kc = f2key((float)(0.5 * (lo[c] + hi[c])));
       centre[3 * t + c] = (float)(0.5 * (lo[c] + hi[c]));
       lmin[c] = min(lmin[c], kc);
@@ -105,30 +128,30 @@ __global__ void __launch_bounds__(kBpBlock) k_tri_boxes(const double* __restrict
     }
   }
   if (bad) atomicCAS(&ctr->status, 0, STATUS_INDEX);
-  for (int c = 0; c < 3; ++c) {
-    smin[c][threadIdx.x] = lmin[c];
-    smax[c][threadIdx.x] = lmax[c];
-  }
-  sext[threadIdx.x] = ext;
-  __syncthreads();
-  for (int w = kBpBlock / 2; w > 0; w >>= 1) {
-    if (threadIdx.x < w) {
-      for (int c = 0; c < 3; ++c) {
-        smin[c][threadIdx.x] = min(smin[c][threadIdx.x], smin[c][threadIdx.x + w]);
-        smax[c][threadIdx.x] = max(smax[c][threadIdx.x], smax[c][threadIdx.x + w]);
-      }
-      sext[threadIdx.x] += sext[threadIdx.x + w];
-    }
-    __syncthreads();
-  }
   // per-block partial bounds and extent sums; the next kernel reduces them (the kernel
   // boundary orders the two)
-  if (threadIdx.x == 0) {
-    for (int c = 0; c < 3; ++c) {
-      part[6 * blockIdx.x + c] = smin[c][0];
-      part[6 * blockIdx.x + 3 + c] = smax[c][0];
+  const int wave = threadIdx.x / 64;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const uint32_t a = wave_min(lmin[c]), b = wave_max(lmax[c]);
+    if (__lane_id() == 63) {
+      sb[c][wave] = a;
+      sb[3 + c][wave] = b;
     }
-    ext_part[blockIdx.x] = sext[0];
+  }
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) ext += __shfl_xor(ext, d);
+  if (__lane_id() == 0) sext[wave] = ext;
+  __syncthreads();
+  if (threadIdx.x < 6) {
+    uint32_t v = sb[threadIdx.x][0];
+    for (int w = 1; w < kW; ++w) v = threadIdx.x < 3 ? min(v, sb[threadIdx.x][w]) : max(v, sb[threadIdx.x][w]);
+    part[6 * blockIdx.x + threadIdx.x] = v;
+  }
+  if (threadIdx.x == 0) {
+    double e = 0.0;
+    for (int w = 0; w < kW; ++w) e += sext[w];
+    ext_part[blockIdx.x] = e;
   }
 }
 
@@ -166,24 +189,23 @@ __global__ void __launch_bounds__(kBpBlock) k_morton(const float* __restrict__ c
     for (int p = threadIdx.x; p < n_prob; p += kBpBlock) bad |= tri_off[p] > tri_off[p + 1];
     if (bad) atomicCAS(&ctr->status, 0, STATUS_INVALID);
   }
-  // every block reduces the per-block bounds of k_tri_boxes (a few KB, cached): a strided
-  // pass per thread, then a tree in LDS
-  __shared__ uint32_t red[6][kBpBlock];
-  __shared__ uint32_t sb[6];
-  uint32_t v[6] = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0u, 0u, 0u};
+  // every block reduces the per-block bounds of k_tri_boxes (a few KB, cached)
+  __shared__ uint32_t wb[6][kBpBlock / 64];
+  uint32_t sb[6] = {0xffffffffu, 0xffffffffu, 0xffffffffu, 0u, 0u, 0u};
   for (int b = threadIdx.x; b < nparts; b += kBpBlock)
-    for (int c = 0; c < 6; ++c) v[c] = c < 3 ? min(v[c], part[6 * b + c]) : max(v[c], part[6 * b + c]);
-  for (int c = 0; c < 6; ++c) red[c][threadIdx.x] = v[c];
-  __syncthreads();
-  for (int w = kBpBlock / 2; w > 0; w >>= 1) {
-    if (threadIdx.x < w)
-      for (int c = 0; c < 6; ++c)
-        red[c][threadIdx.x] = c < 3 ? min(red[c][threadIdx.x], red[c][threadIdx.x + w])
-                                    : max(red[c][threadIdx.x], red[c][threadIdx.x + w]);
-    __syncthreads();
+    for (int c = 0; c < 6; ++c) sb[c] = c < 3 ? min(sb[c], part[6 * b + c]) : max(sb[c], part[6 * b + c]);
+#pragma unroll
+  for (int c = 0; c < 6; ++c) {
+    const uint32_t v = c < 3 ? wave_min(sb[c]) : wave_max(sb[c]);
+    if (__lane_id() == 63) wb[c][threadIdx.x / 64] = v;
   }
-  if (threadIdx.x < 6) sb[threadIdx.x] = red[threadIdx.x][0];
   __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 6; ++c) {
+    sb[c] = wb[c][0];
+#pragma unroll
+    for (int w = 1; w < kBpBlock / 64; ++w) sb[c] = c < 3 ? min(sb[c], wb[c][w]) : max(sb[c], wb[c][w]);
+  }
   float lo[3], inv[3];
   for (int c = 0; c < 3; ++c) {
     lo[c] = key2f(sb[c]);
@@ -284,22 +306,55 @@ __device__ __forceinline__ Box32 box_union(const Box32& a, const Box32& b) {
   return r;
 }
 
-// The shared vertex of up to four triangles (vertex ids, or kEmpty rows for absent leaves): the
-// first vertex of the first present one that every present one holds.
-__device__ __forceinline__ int32_t common_of_leaves(const int3& t0, const int3& t1, const int3& t2, const int3& t3) {
-  const int3 f = t0.x != kEmpty ? t0 : (t1.x != kEmpty ? t1 : (t2.x != kEmpty ? t2 : t3));
-  if (f.x == kEmpty) return kEmpty;
-  const auto holds = [](const int3& t, int32_t v) { return t.x == kEmpty || t.x == v || t.y == v || t.z == v; };
-  const int32_t cand[3] = {f.x, f.y, f.z};
+// The box of the lanes that the pattern pairs, united (every lane of the wave must call)
+template <int kCtrl>
+__device__ __forceinline__ Box32 box_union_dpp(const Box32& a) {
+  Box32 b;
 #pragma unroll
-  for (int u = 0; u < 3; ++u)
-    if (holds(t0, cand[u]) && holds(t1, cand[u]) && holds(t2, cand[u]) && holds(t3, cand[u])) return cand[u];
-  return kNoCommon;
+  for (int c = 0; c < 3; ++c) {
+    b.lo[c] = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(a.lo[c]), kCtrl, 0xf, 0xf, true));
+    b.hi[c] = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(a.hi[c]), kCtrl, 0xf, 0xf, true));
+  }
+  set_common(b, __builtin_amdgcn_mov_dpp(box_common(a), kCtrl, 0xf, 0xf, true));
+  return box_union(a, b);
+}
+// of a quad of lanes, a row of 16 from its quads', the wave from its rows', in every lane
+__device__ __forceinline__ Box32 quad_union(const Box32& a) { return box_union_dpp<0x4e>(box_union_dpp<0xb1>(a)); }
+__device__ __forceinline__ Box32 row_union(const Box32& a) { return box_union_dpp<0x128>(box_union_dpp<0x124>(a)); }
+__device__ __forceinline__ Box32 wave_union(Box32 a) {
+#pragma unroll
+  for (int d = 16; d < 64; d <<= 1) {
+    Box32 b;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      b.lo[c] = __shfl_xor(a.lo[c], d);
+      b.hi[c] = __shfl_xor(a.hi[c], d);
+    }
+    set_common(b, __shfl_xor(box_common(a), d));
+    a = box_union(a, b);
+  }
+  return a;
+}
+
+// The shared vertex of the up to four triangles of a quad of lanes (x = kEmpty: no triangle, in
+// the last lanes): the first vertex of the first that every present one holds.
+__device__ __forceinline__ int32_t common_of_quad(const int3& t) {
+  const int32_t f[3] = {__builtin_amdgcn_mov_dpp(t.x, 0, 0xf, 0xf, true), __builtin_amdgcn_mov_dpp(t.y, 0, 0xf, 0xf, true),
+                        __builtin_amdgcn_mov_dpp(t.z, 0, 0xf, 0xf, true)};
+  int held = 0;
+#pragma unroll
+  for (int u = 0; u < 3; ++u) held |= (int)(t.x == kEmpty || t.x == f[u] || t.y == f[u] || t.z == f[u]) << u;
+  held &= __builtin_amdgcn_mov_dpp(held, 0xb1, 0xf, 0xf, true);
+  held &= __builtin_amdgcn_mov_dpp(held, 0x4e, 0xf, 0xf, true);
+  if (f[0] == kEmpty) return kEmpty;
+  return held & 1 ? f[0] : held & 2 ? f[1] : held & 4 ? f[2] : kNoCommon;
 }
 
 // Reduces levels l0+1 .. l0+4 (256 threads) or l0+1 .. l0+5 (1024 threads) from the boxes of
 // level l0 (l0 = 0: made from the sorted leaves, which are written too).  Block b owns level-l0
-// nodes [kThreads b, kThreads (b + 1)).
+// nodes [kThreads b, kThreads (b + 1)).  A wave makes three levels in registers, the block's first
+// wave the last one or two from the waves' boxes.  Bound by the gathers of the leaf pass: 177 us
+// for 4,194,304 leaves (186 with every level through LDS and two barriers); 7.6 us for 130,050.
 // For a batch (tri_off != NULL) the leaf pass also writes qend[k]: the end of the sorted range of
 // the problem owning leaf k (problem p + 1 starts at the offset of its first bucket).
 template <int kThreads>
@@ -309,8 +364,7 @@ __global__ void __launch_bounds__(kThreads) k_levels(int l0, Levels lv, const do
                                                      LeafIds* __restrict__ leaves, const int64_t* __restrict__ tri_off,
                                                      int n_prob, int mbits, const int32_t* __restrict__ offset,
                                                      int32_t* __restrict__ qend) {
-  __shared__ Box32 sh[kThreads];
-  __shared__ int3 sv[kThreads];  // the leaves' vertex ids (leaf pass only)
+  __shared__ Box32 sh[kThreads / 64];
   const int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   Box32 bx;
   for (int c = 0; c < 3; ++c) {
@@ -344,30 +398,32 @@ __global__ void __launch_bounds__(kThreads) k_levels(int l0, Levels lv, const do
       bx = boxes[lv.off[l0] + k];
     }
   }
-  sh[threadIdx.x] = bx;
-  if (l0 == 0) sv[threadIdx.x] = tv;
-  __syncthreads();
   constexpr int kLevels = kThreads == 256 ? 4 : 5;
   static_assert(kThreads == 1 << (2 * kLevels), "a block reduces kThreads nodes to one");
-  for (int j = 1; j <= kLevels && l0 + j <= lv.L; ++j) {
-    const int cnt = kThreads >> (2 * j);
-    Box32 r;
-    const bool act = threadIdx.x < cnt;
-    if (act) {
-      r = box_union(box_union(sh[4 * threadIdx.x], sh[4 * threadIdx.x + 1]),
-                    box_union(sh[4 * threadIdx.x + 2], sh[4 * threadIdx.x + 3]));
-      if (l0 == 0 && j == 1) {  // level 1: the vertex its (up to four) triangles share
-        set_common(r, common_of_leaves(sv[4 * threadIdx.x], sv[4 * threadIdx.x + 1], sv[4 * threadIdx.x + 2],
-                                       sv[4 * threadIdx.x + 3]));
-      }
-    }
-    __syncthreads();
-    if (act) {
-      sh[threadIdx.x] = r;
-      const int64_t node = (int64_t)blockIdx.x * cnt + threadIdx.x;
-      if (node < lv.m[l0 + j]) boxes[lv.off[l0 + j] + node] = r;
-    }
-    __syncthreads();
+  const int lane = __lane_id();
+  // level l0 + j, of which this lane's node is the k >> 2j-th, one lane of each node writing
+  const auto put = [&](int j, const Box32& r, int64_t node, bool writes) {
+    if (writes && l0 + j <= lv.L && node < lv.m[l0 + j]) boxes[lv.off[l0 + j] + node] = r;
+  };
+  Box32 r = quad_union(bx);
+  if (l0 == 0) set_common(r, common_of_quad(tv));  // level 1: the vertex its triangles share
+  put(1, r, k >> 2, (lane & 3) == 0);
+  if (l0 + 2 > lv.L) return;  // (the whole grid)
+  r = row_union(r);
+  put(2, r, k >> 4, (lane & 15) == 0);
+  if (l0 + 3 > lv.L) return;
+  r = wave_union(r);
+  put(3, r, k >> 6, lane == 0);
+  if (l0 + 4 > lv.L) return;
+  if (lane == 0) sh[threadIdx.x / 64] = r;
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  constexpr int kN = kThreads / 64;  // 4 or 16 boxes left
+  r = quad_union(sh[lane < kN ? lane : kN - 1]);
+  put(4, r, (int64_t)blockIdx.x * (kN / 4) + lane / 4, lane < kN && (lane & 3) == 0);
+  if constexpr (kLevels == 5) {
+    r = row_union(r);
+    put(5, r, blockIdx.x, lane == 0);
   }
 }
 
@@ -1450,7 +1506,7 @@ hipError_t launch_broadphase(Ctx* c, const ttie_mesh* m, int method, const doubl
     const int64_t nbuckets = (int64_t)1 << (pbits + mbits);
     int32_t* hist = wsp<int32_t>(c, L.bvh_hist);
     int32_t* offset = wsp<int32_t>(c, L.bvh_offset);
-    k_tri_boxes<<<gb, kBpBlock, 0, s>>>(m->x, x_end, m->n_verts, m->tris, nt, tbox, centre,
+    k_tri_boxes<<<gb, kBpBlock, 0, s>>>(m->x, x_end, m->n_verts, m->tris, nt, tbox, wsp<float>(c, L.bvh_centroid),
                                         wsp<uint32_t>(c, L.bvh_part), wsp<double>(c, L.bvh_ext), npairs, ctr);
     k_morton<<<bp_grid(nt), kBpBlock, 0, s>>>(centre, nt, wsp<uint32_t>(c, L.bvh_part), (int)gb, tri_off, n_prob,
                                               mbits, hist, k1, v1, ctr);
