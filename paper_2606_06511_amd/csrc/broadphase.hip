@@ -568,20 +568,23 @@ constexpr int kStackWide = kStack - 48 - 48;
 constexpr uint32_t kGuard = (1u << 10) | (1u << 21) | (1u << 31);
 // The budget (a launch parameter, 128 by default) counts three units for a step of 16 nodes and
 // for 64 pairs tested, about 40 steps in all, where a usual group takes 20: candidates are
-// handed over from there on.  Nodes are only handed over after many more steps (twice the
-// budget), since a part that starts from one node repeats the group's setup for few candidates.
+// handed over from there on, 64 in a batch.  Nodes are handed over after 3/8 of the budget in
+// steps, which few groups reach, since a part that starts from one node repeats the group's
+// setup for few candidates.
 // Measured, broad phase of the 4,194,304-triangle sphere at 64, 96, 128, 192: 1.38, 1.25, 1.23,
 // 1.22 ms; of the 1,048,576-triangle one: 0.40, 0.39, 0.41, 0.43 ms.
 // With few groups -- all resident at once, or nearly: 5,120 waves are -- the kernel lasts as long as its
-// slowest wave while most of the chip is idle, so there candidates go from half the budget on,
-// in parts of 16, and nodes after 3/8 of that many steps.  The broad phase of a 36,000-triangle
-// batch of three meshes of different sizes then takes 92 us instead of 168, of a 126,000-triangle
-// batch of six 116 instead of 160, of a 63,000-triangle sphere with fans at its poles 122 instead of 157,
-// of a 370,000-triangle one 265 instead of 308, of cloths of 130,000 and 149,000, whose groups are
-// alike, 96 as before and 95 instead of 90.  With it, a 1,207,458-triangle cloth takes 292 us
-// instead of 278, the 1,048,576-triangle sphere 393 instead of 419.
-constexpr int64_t kTravFew = 1 << 19;  // triangles
-constexpr int kPart = 16;              // candidates
+// slowest wave while most of the chip is idle, so there the budget is halved, and while the second
+// kernel has too few batches to fill the chip it takes each in four parts.  The broad phase of a
+// 36,000-triangle batch of three meshes of different sizes then takes 89 us instead of 168, of a
+// 126,000-triangle batch of six 113 instead of 160, of a 63,000-triangle sphere with fans at its poles 120
+// instead of 157, of a 370,000-triangle one 270 instead of 308, of cloths of 130,000 and 149,000,
+// whose groups are alike, 93 instead of 96 and 93 instead of 90.  Half the budget on a 1,207,458-triangle
+// cloth costs 292 us instead of 278.  Four parts on spheres of 665,000 and 1,048,576 triangles: 297 us
+// instead of 331 and 393 instead of 415; on the cloth 276 instead of 274, on a 64-problem batch
+// and a sphere of 4,194,304 1.47 instead of 1.455 ms and 1.26 instead of 1.24.
+constexpr int64_t kTravFew = 1 << 19;    // triangles up to which the budget is halved
+constexpr int64_t kTravParts = 1 << 20;  // and up to which batches are taken in parts
 // Queries overlapping one candidate from which adjacency is tested before the pairs are listed:
 // 64 more comparisons a batch, which pay where nearly the whole group shares a vertex with it.
 constexpr int kDense = 48;
@@ -747,10 +750,10 @@ __device__ __forceinline__ void row_tests(uint32_t& bits, uint32_t qlo, uint32_t
 
 // kVA: pairs sharing exactly one vertex are candidates (a template argument, so the default
 // keeps the plain shared-vertex test).  kHeavy: the rest of a search handed over by another
-// wave: from the node `start`, or the tests of `batch`.  kFew: see kTravFew.
-template <bool kVA, bool kHeavy, bool kFew, class Emitter>
+// wave: from the node `start`, or the tests of `most` candidates of `batch` from `first` on.
+template <bool kVA, bool kHeavy, class Emitter>
 __device__ __forceinline__ void search_group(TravWave& sh, const int32_t* lm, const uint32_t* loff, int32_t n, int L,
-                                             int32_t g, uint32_t start, const TravBatch* batch,
+                                             int32_t g, uint32_t start, const TravBatch* batch, int first, int most,
                                              const Box32* __restrict__ boxes,
                                              const LeafIds* __restrict__ leaves, const double* __restrict__ tbox,
                                              const int32_t* __restrict__ qend, const TravHeavy& heavy, int budget,
@@ -907,8 +910,8 @@ __device__ __forceinline__ void search_group(TravWave& sh, const int32_t* lm, co
   int sp = 0;
   if (kHeavy) {
     if (batch) {
-      nc = batch->count;
-      if (lane < nc) sh.cleaf[lane] = batch->leaf[lane];
+      nc = max(0, min(batch->count - first, most));  // (none in a part past the last one)
+      if (lane < nc) sh.cleaf[lane] = batch->leaf[first + lane];
     } else {
       if (lane == 0) sh.stack[0] = start;
       sp = 1;
@@ -929,7 +932,7 @@ __device__ __forceinline__ void search_group(TravWave& sh, const int32_t* lm, co
   // the group's own leaves are the first candidates, then those the search finds, 64 at a time
   for (bool own = !kHeavy;; own = false) {
     while (!own && nc < 64 && sp > 0) {
-      if (may_defer && steps > (kFew ? 3 * budget / 8 : 2 * budget)) {
+      if (may_defer && steps > 3 * budget / 8) {
         // the nodes still to be searched, as far as the list has room
         uint32_t base = 0;
         if (lane == 0) base = atomicAdd(&ctr->n_heavy, (uint32_t)sp);
@@ -969,27 +972,15 @@ __device__ __forceinline__ void search_group(TravWave& sh, const int32_t* lm, co
     bool handed = false;
     if (!kHeavy && !own && work > budget) {  // over the budget: left to another wave, if the list has room
       uint32_t at = 0;
-      if constexpr (kFew) {  // in parts; the list's last places, too few for all parts, become empty batches
-        const int parts = (cnt + kPart - 1) / kPart;
-        if (lane == 0) at = atomicAdd(&ctr->n_batches, (uint32_t)parts);
-        at = __shfl(at, 0);
-        handed = at < heavy.batch_cap && heavy.batch_cap - at >= (uint32_t)parts;
-        if (lane < parts && at + lane < heavy.batch_cap) {
-          heavy.batches[at + lane].group = g;
-          heavy.batches[at + lane].count = handed ? min(cnt - lane * kPart, kPart) : 0;
+      if (lane == 0) at = atomicAdd(&ctr->n_batches, 1u);
+      at = __shfl(at, 0);
+      if (at < heavy.batch_cap) {
+        if (lane == 0) {
+          heavy.batches[at].group = g;
+          heavy.batches[at].count = cnt;
         }
-        if (handed && lane < cnt) heavy.batches[at + lane / kPart].leaf[lane % kPart] = sh.cleaf[lane];
-      } else {
-        if (lane == 0) at = atomicAdd(&ctr->n_batches, 1u);
-        at = __shfl(at, 0);
-        if (at < heavy.batch_cap) {
-          if (lane == 0) {
-            heavy.batches[at].group = g;
-            heavy.batches[at].count = cnt;
-          }
-          if (lane < cnt) heavy.batches[at].leaf[lane] = sh.cleaf[lane];
-          handed = true;
-        }
+        if (lane < cnt) heavy.batches[at].leaf[lane] = sh.cleaf[lane];
+        handed = true;
       }
     }
     if (!handed) {
@@ -1034,7 +1025,7 @@ __device__ __forceinline__ void end_emit(Emitter& em, Shared& sh, const PairSink
   em.store(base, o);
 }
 
-template <bool kVA, bool kFew>
+template <bool kVA>
 __global__ void __launch_bounds__(kTravThreads, kTravMinWaves) k_traverse(int64_t n64, Levels lv, const Box32* __restrict__ boxes,
                                                            const LeafIds* __restrict__ leaves,
                                                            const double* __restrict__ tbox,
@@ -1048,31 +1039,33 @@ __global__ void __launch_bounds__(kTravThreads, kTravMinWaves) k_traverse(int64_
   const int64_t g = xcd_block(blockIdx.x, gridDim.x) * kTravWaves + wave;
   GroupEmitter em{&sh.stage[wave], 0, 0};
   if (g * kGroup < n64)
-    search_group<kVA, false, kFew>(sh.w[wave], sh.lm, sh.loff, (int32_t)n64, lv.L, (int32_t)g, 0u, nullptr, boxes, leaves,
-                             tbox, qend, heavy, budget, em, sink, ctr);
+    search_group<kVA, false>(sh.w[wave], sh.lm, sh.loff, (int32_t)n64, lv.L, (int32_t)g, 0u, nullptr, 0, 0, boxes,
+                             leaves, tbox, qend, heavy, budget, em, sink, ctr);
   end_emit(em, sh, sink);
 }
 
-// What the waves over their budget handed over, a wave per batch or node.
+// What the waves over their budget handed over, a wave per node, batch or part of a batch (parts:
+// 1 or 4 of each).
 template <bool kVA>
 __global__ void __launch_bounds__(kTravThreads, kTravMinWaves) k_traverse_heavy(int64_t n64, Levels lv, const Box32* __restrict__ boxes,
                                                                  const LeafIds* __restrict__ leaves,
                                                                  const double* __restrict__ tbox,
                                                                  const int32_t* __restrict__ qend, TravHeavy heavy,
-                                                                 int32_t* pairs, int64_t cap,
+                                                                 int parts, int32_t* pairs, int64_t cap,
                                                                  unsigned long long* npairs, Counters* ctr) {
   __shared__ TravShared<PairEmitter> sh;
   const PairSink sink{pairs, cap, npairs, &ctr->status};
-  const int64_t nb = min(ctr->n_batches, heavy.batch_cap), nn = min(ctr->n_heavy, heavy.node_cap);
+  const int most = 64 / parts;  // candidates of a batch that a wave takes
+  const int64_t nb = (int64_t)parts * min(ctr->n_batches, heavy.batch_cap), nn = min(ctr->n_heavy, heavy.node_cap);
   if ((int64_t)blockIdx.x * kTravWaves >= nb + nn) return;  // (the whole block)
   level_table(sh, lv);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
   PairEmitter em{&sh.stage[wave], 0, 0};
   for (int64_t i = (int64_t)blockIdx.x * kTravWaves + wave; i < nb + nn; i += (int64_t)gridDim.x * kTravWaves) {
-    const TravBatch* batch = i < nb ? heavy.batches + i : nullptr;
+    const TravBatch* batch = i < nb ? heavy.batches + i / parts : nullptr;
     const TravNode node = i < nb ? TravNode{batch->group, 0u} : heavy.nodes[i - nb];
-    search_group<kVA, true, false>(sh.w[wave], sh.lm, sh.loff, (int32_t)n64, lv.L, node.group, node.node, batch, boxes, leaves,
-                            tbox, qend, heavy, 0, em, sink, ctr);
+    search_group<kVA, true>(sh.w[wave], sh.lm, sh.loff, (int32_t)n64, lv.L, node.group, node.node, batch,
+                            (int)(i % parts) * most, most, boxes, leaves, tbox, qend, heavy, 0, em, sink, ctr);
   }
   end_emit(em, sh, sink);
 }
@@ -1537,16 +1530,16 @@ hipError_t launch_broadphase(Ctx* c, const ttie_mesh* m, int method, const doubl
     const TravHeavy heavy{wsp<TravNode>(c, L.bvh_heavy), wsp<TravBatch>(c, L.bvh_heavy + half),
                           (uint32_t)(half / sizeof(TravNode)), (uint32_t)(half / sizeof(TravBatch))};
     const int budget = (int)ctx_param(c, TTIE_PARAM_TRAV_BUDGET);
-    const bool few = nt <= kTravFew;
     const int32_t* qe = tri_off ? qend : nullptr;
-    const auto traverse = few ? (va ? k_traverse<true, true> : k_traverse<false, true>)
-                              : (va ? k_traverse<true, false> : k_traverse<false, false>);
+    const auto traverse = va ? k_traverse<true> : k_traverse<false>;
     const auto traverse_heavy = va ? k_traverse_heavy<true> : k_traverse_heavy<false>;
-    traverse<<<(unsigned)nb, kTravThreads, 0, s>>>(nt, lv, boxes, leaves, tbox, qe, heavy, few ? (budget + 1) / 2 : budget, pairs,
-                                                   capacity, npairs, ctr);
+    traverse<<<(unsigned)nb, kTravThreads, 0, s>>>(nt, lv, boxes, leaves, tbox, qe, heavy,
+                                                   nt <= kTravFew ? (budget + 1) / 2 : budget, pairs, capacity, npairs,
+                                                   ctr);
     stage_end(c, TTIE_STAGE_BP_TRAVERSE, s);
     stage_begin(c, TTIE_STAGE_BP_HEAVY, s);
-    traverse_heavy<<<1024, kTravThreads, 0, s>>>(nt, lv, boxes, leaves, tbox, qe, heavy, pairs, capacity, npairs, ctr);
+    traverse_heavy<<<1024, kTravThreads, 0, s>>>(nt, lv, boxes, leaves, tbox, qe, heavy, nt <= kTravParts ? 4 : 1, pairs,
+                                                 capacity, npairs, ctr);
     stage_end(c, TTIE_STAGE_BP_HEAVY, s);
   }
   return hipGetLastError();

@@ -125,11 +125,11 @@ def test_problems_inside_groups():
     assert np.array_equal(got, ref)
 
 
-@pytest.mark.parametrize("n,budget", [(524288, 16), (524288, 0), (524289, 16), (524289, 0)])
+@pytest.mark.parametrize("n,budget", [(524288, 16), (524288, 0), (524289, 16), (524289, 0), (1048577, 16), (1048577, 0)])
 def test_both_handover_rules(n, budget):
-    """On both sides of the size from which searches are handed over later and whole, against the
-    candidates of the spatial hash; a tenth of the triangles in a dense heap, whose searches are
-    over any budget."""
+    """On both sides of the sizes from which searches are handed over later, and taken up whole,
+    against the candidates of the spatial hash; a tenth of the triangles in a dense heap, whose
+    searches are over any budget."""
     import torch
 
     from paper_2606_06511_amd import ttie
@@ -140,7 +140,7 @@ def test_both_handover_rules(n, budget):
     x = torch.from_numpy((c + rng.normal(0.0, 0.15, (n, 3, 3))).reshape(-1, 3)).cuda()
     tris = torch.arange(3 * n, dtype=torch.int32, device="cuda").reshape(n, 3)
     ctx = ttie.Context(0)
-    cap = 4_000_000
+    cap = 16_000_000
     ctx.reserve(3 * n, n, cap, max_hits=64)
     ctx.set_param(ttie.PARAM_TRAV_BUDGET, budget)
     keys = []
