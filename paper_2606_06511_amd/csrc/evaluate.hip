@@ -370,7 +370,13 @@ __global__ void __launch_bounds__(kBlock) k_screen_flag(const double* __restrict
 // dependent loads for one or two pairs).  A pair that straddles both ways comes with its exact
 // plane sides, so the plane distances are computed again for a hit only.  The deferred candidates
 // of the lists and its own it gathers in LDS, and appends to the one list of k_screen_exact.
-constexpr int kMergeChunks = 16;
+constexpr int kMergeChunks = 8;
+// Blocks of k_screen and k_screen_flag, where the caller sets no number: as many as the chip holds
+// (five waves a SIMD), so that no round of blocks is nearly empty and none starts without
+// work, and twice that for a list that may be longer than kScreenShort, whose waves differ
+// more.  Evaluations with 4096 blocks, 2560 and 1280: 162,000 candidates of a capacity of 2^20 182,
+// 173 and 166 us; 2.0 M 134, 129 and 129 us; 4.6 M 600, 588 and 599; 20.8 M 515, 503 and 527.
+constexpr int64_t kScreenBlocks = 1280, kScreenShort = 1 << 22;
 constexpr int kLate = 512;        // deferred candidates a wave gathers before it reserves their places
 constexpr int64_t kMaxUnits = 65536 * kWaves;  // entries of nfull: chunks of a 65536-block grid, or tiles
 
@@ -458,7 +464,7 @@ __global__ void __launch_bounds__(kBlock) k_screen_full(const double* __restrict
 // uncertain sign in fixed point it took 553 us for the 240,000 of a 64-problem batch (3.6 M
 // candidates), bound by the accumulators in scratch memory; with double-word signs, fixed point
 // for what they leave open and for the distances of hits, and the accumulators in shared
-// memory, 104 us.  Two waves fit a SIMD (212 registers), hence the grid of 2048 waves.
+// memory, 104 us.  The grid is a wave per SIMD (two would fit: as fast).
 __global__ void __launch_bounds__(kExactThreads) k_screen_exact(const double* __restrict__ x, int64_t nv,
                                                          const int32_t* __restrict__ tris, int64_t nt,
                                                          const int32_t* __restrict__ pairs, int64_t max_pairs,
@@ -1480,7 +1486,9 @@ static hipError_t eval_impl(Ctx* c, const ttie_mesh* m, const int32_t* pairs, co
 
   stage_begin(c, TTIE_STAGE_SCREEN, s);
   // both screening kernels split the list the same way: the same grid
-  const unsigned gscreen = grid_for(pair_cap, (unsigned)ctx_param(c, TTIE_PARAM_SCREEN_BLOCKS));
+  const int64_t set = c->param[TTIE_PARAM_SCREEN_BLOCKS];
+  const unsigned gscreen =
+      grid_for(pair_cap, (unsigned)(set ? set : pair_cap <= kScreenShort ? kScreenBlocks : 2 * kScreenBlocks));
   uint16_t* fsig = wsp<uint16_t>(c, L.fsig);
   // the screening's units: one chunk per wave, or tiles from a queue (at most kMaxUnits of
   // them, the length of nfull)
@@ -1497,7 +1505,7 @@ static hipError_t eval_impl(Ctx* c, const ttie_mesh* m, const int32_t* pairs, co
                                   hits, max_hits, defer, full, fsig, nfull, ctr, flags, pair_T);
   stage_end(c, TTIE_STAGE_SCREEN, s);
   stage_begin(c, TTIE_STAGE_SCREEN_EXACT, s);
-  k_screen_exact<<<4 * grid_for(pair_cap, 512), kExactThreads, 0, s>>>(m->x, nv, m->tris, m->n_tris, pairs, pair_cap, half, va,
+  k_screen_exact<<<2 * grid_for(pair_cap, 512), kExactThreads, 0, s>>>(m->x, nv, m->tris, m->n_tris, pairs, pair_cap, half, va,
                                                             hits, max_hits, defer, ctr, flags, pair_T);
   stage_end(c, TTIE_STAGE_SCREEN_EXACT, s);
   stage_begin(c, TTIE_STAGE_DERIVS, s);
