@@ -215,17 +215,20 @@ __device__ __forceinline__ int screen_stage1(int64_t p, const double* x, int64_t
   return STEP_FULL;
 }
 
-// The candidate list is split into one contiguous chunk per wave (a multiple of 64 long, the
-// same split in both screening kernels).  Blocks are renumbered so that each XCD screens a
+// The candidate list is split into one contiguous chunk per wave (the same split in all screening
+// kernels): batches of 64, of which every wave takes as many as the others or one more, spread over
+// the grid.  (Chunks of one length left up to half of the waves idle where that is a few batches.)  Blocks are renumbered so that each XCD screens a
 // contiguous range of the list (its L2 then sees one region of the mesh).
+__device__ __forceinline__ int64_t chunk_start(int64_t np, int64_t nw, int64_t w) {
+  return min(np, (int64_t)((uint64_t)w * (uint64_t)((np + 63) / 64) / (uint64_t)nw) * 64);
+}
 __device__ __forceinline__ void wave_chunk(int64_t np, int64_t& beg, int64_t& end, int64_t& wid) {
   const int64_t G = gridDim.x;
   const int64_t lb = (G % 8 == 0) ? xcd_block(blockIdx.x, G) : (int64_t)blockIdx.x;
   const int64_t nw = G * kWaves;
-  const int64_t chunk = ((np + nw - 1) / nw + 63) / 64 * 64;
   wid = lb * kWaves + threadIdx.x / 64;
-  beg = min(np, wid * chunk);
-  end = min(np, beg + chunk);
+  beg = chunk_start(np, nw, wid);
+  end = chunk_start(np, nw, wid + 1);
 }
 
 // First stage over the candidate list, one lane per candidate.  A wave writes the candidates it
@@ -234,7 +237,7 @@ __device__ __forceinline__ void wave_chunk(int64_t np, int64_t& beg, int64_t& en
 // evaluation (read by the calls after it) before k_derivs marks this one's, and checks every
 // coordinate against the exact predicates' domain (a violation is reported, never acted on: out
 // of it the exact arithmetic only loses exactness, it stays within its arrays).
-__global__ void __launch_bounds__(kBlock) k_screen(const double* __restrict__ x, int64_t nv,
+__global__ void __launch_bounds__(kBlock, 6) k_screen(const double* __restrict__ x, int64_t nv,
                                                    const int32_t* __restrict__ tris, int64_t nt,
                                                    const int32_t* __restrict__ pairs, const int64_t* n_pairs_dev,
                                                    int64_t max_pairs, int va,
@@ -372,11 +375,12 @@ __global__ void __launch_bounds__(kBlock) k_screen_flag(const double* __restrict
 // of the lists and its own it gathers in LDS, and appends to the one list of k_screen_exact.
 constexpr int kMergeChunks = 8;
 // Blocks of k_screen and k_screen_flag, where the caller sets no number: as many as the chip holds
-// (five waves a SIMD), so that no round of blocks is nearly empty and none starts without
-// work, and twice that for a list that may be longer than kScreenShort, whose waves differ
-// more.  Evaluations with 4096 blocks, 2560 and 1280: 162,000 candidates of a capacity of 2^20 182,
-// 173 and 166 us; 2.0 M 134, 129 and 129 us; 4.6 M 600, 588 and 599; 20.8 M 515, 503 and 527.
-constexpr int64_t kScreenBlocks = 1280, kScreenShort = 1 << 22;
+// of k_screen (six waves a SIMD, for which it gives up 4 registers), so that none starts without
+// work and no round of them is nearly empty.  Evaluations (162,000 candidates: the step) with 4096 blocks of five
+// waves a SIMD and chunks of one length, and now: 162,000 candidates 182 and 161 us, 184,000 85 and 65,
+// 2.0 M 134 and 127.5, 4.6 M (the step) 600 and 581, 20.8 M 515 and 489.  (1280 blocks of five waves: 160, 65, 129, 585,
+// 500.  Twice 1536 for long lists: 130 us for the 2.0 M, 481 for the 20.8 M.)
+constexpr int64_t kScreenBlocks = 1536;
 constexpr int kLate = 512;        // deferred candidates a wave gathers before it reserves their places
 constexpr int64_t kMaxUnits = 65536 * kWaves;  // entries of nfull: chunks of a 65536-block grid, or tiles
 
@@ -391,14 +395,16 @@ __global__ void __launch_bounds__(kBlock) k_screen_full(const double* __restrict
                                                         const int32_t* __restrict__ nfull, Counters* ctr,
                                                         uint8_t* __restrict__ flags, double* __restrict__ pair_T) {
   const int64_t np = min(*n_pairs_dev, max_pairs);
-  // the units' length and count: the tiles, or the chunks of the screening grid's n_chunks
-  // waves (as wave_chunk computes them there)
-  const int64_t chunk = tile ? tile : ((np + n_chunks - 1) / n_chunks + 63) / 64 * 64;
-  if (tile) n_chunks = (np + tile - 1) / tile;
+  // the units: the tiles, or the chunks of the screening grid's n_chunks waves
+  const int64_t n_units = tile ? (np + tile - 1) / tile : n_chunks;
   const int lane = __lane_id();
   const int64_t c0 = ((int64_t)blockIdx.x * kWaves + threadIdx.x / 64) * kMergeChunks;
   int32_t cnt = 0;
-  if (lane < kMergeChunks && c0 + lane < n_chunks) cnt = nfull[c0 + lane];
+  int64_t start = 0;
+  if (lane < kMergeChunks && c0 + lane < n_units) {
+    cnt = nfull[c0 + lane];
+    start = tile ? (c0 + lane) * tile : chunk_start(np, n_chunks, c0 + lane);
+  }
   // inclusive prefix of the chunk counts, then every lane holds all of them
   int32_t incl = cnt;
 #pragma unroll
@@ -432,17 +438,18 @@ __global__ void __launch_bounds__(kBlock) k_screen_full(const double* __restrict
     const int32_t e = e0 + lane;
     int64_t p = -1;
     uint32_t code = 0;
-    if (e < total) {
-      // the chunk holding entry e, and e's place in its list
-      int j = 0;
-      int32_t below = 0;
+    // the chunk holding entry e, and e's place in its list
+    int j = 0;
+    int32_t below = 0;
 #pragma unroll
-      for (int k = 0; k < kMergeChunks - 1; ++k)
-        if (e >= pre[k]) {
-          j = k + 1;
-          below = pre[k];
-        }
-      const int64_t at = min(np, (c0 + j) * chunk) + (e - below);
+    for (int k = 0; k < kMergeChunks - 1; ++k)
+      if (e >= pre[k]) {
+        j = k + 1;
+        below = pre[k];
+      }
+    const int64_t beg = __shfl(start, j);
+    if (e < total) {
+      const int64_t at = beg + (e - below);
       p = full[at];
       code = fsig[at];
     }
@@ -1487,8 +1494,7 @@ static hipError_t eval_impl(Ctx* c, const ttie_mesh* m, const int32_t* pairs, co
   stage_begin(c, TTIE_STAGE_SCREEN, s);
   // both screening kernels split the list the same way: the same grid
   const int64_t set = c->param[TTIE_PARAM_SCREEN_BLOCKS];
-  const unsigned gscreen =
-      grid_for(pair_cap, (unsigned)(set ? set : pair_cap <= kScreenShort ? kScreenBlocks : 2 * kScreenBlocks));
+  const unsigned gscreen = grid_for(pair_cap, (unsigned)(set ? set : kScreenBlocks));
   uint16_t* fsig = wsp<uint16_t>(c, L.fsig);
   // the screening's units: one chunk per wave, or tiles from a queue (at most kMaxUnits of
   // them, the length of nfull)

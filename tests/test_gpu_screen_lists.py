@@ -55,22 +55,24 @@ def test_deferred_lists(how, tile):
     assert int(out["n_hits"].item()) == int((ref == 1).sum())
 
 
-@pytest.mark.parametrize("capacity", [1 << 22, (1 << 22) + 1])
-def test_both_grids(capacity):
-    """On both sides of the pair capacity at which the screening's grid changes."""
+@pytest.mark.parametrize("blocks", [0, 64])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 64 * 256 - 1, 64 * 256 + 1, 3 * 64 * 256 + 63, 64 * 6144 - 1, 64 * 6144 + 65])
+def test_chunks_of_the_list(n, blocks):
+    """Lists around a batch of 64 and around a batch for each of the grid's waves (256 with 64
+    blocks, 6,144 by default), which take one batch more or less than each other."""
     import torch
 
     from paper_2606_06511_amd import ttie, workloads
 
     x, tris = workloads.folded_cloth(2, n=64)
-    pairs = oracle.pairs(x, tris)
-    ref = oracle.evaluate(x, tris, pairs, hessian=False)
+    pairs = oracle.pairs(x, tris).astype(np.int32)
+    ref = oracle.evaluate(x, tris, pairs, hessian=False)["flags"]
+    take = np.random.default_rng(n).integers(0, len(pairs), n)
     ctx = ttie.Context(0)
-    ctx.reserve(len(x), len(tris), capacity, max_hits=1 << 12)
-    buf = torch.zeros((capacity, 2), dtype=torch.int32, device="cuda")
-    buf[: len(pairs)] = torch.from_numpy(pairs.astype(np.int32)).cuda()
-    out = ctx.evaluate(torch.from_numpy(x).cuda(), torch.from_numpy(tris).cuda(), buf,
-                       torch.tensor([len(pairs)], device="cuda"), hessian=False, flags=True)
+    ctx.reserve(len(x), len(tris), n, max_hits=max(64, int((ref[take] == 1).sum())))
+    ctx.set_param(ttie.PARAM_SCREEN_BLOCKS, blocks)
+    out = ctx.evaluate(torch.from_numpy(x).cuda(), torch.from_numpy(tris).cuda(),
+                       torch.from_numpy(pairs[take]).cuda(), hessian=False, flags=True)
     ctx.check()
-    assert np.array_equal(out["flags"][: len(pairs)].cpu().numpy(), ref["flags"])
-    assert int(out["n_hits"].item()) == len(ref["hit_pair"]) > 0
+    assert np.array_equal(out["flags"].cpu().numpy(), ref[take])
+    assert int(out["n_hits"].item()) == int((ref[take] == 1).sum())
