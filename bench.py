@@ -124,11 +124,11 @@ def stage_bytes(stage, nv, nt, P, H, nnzb, prec_bytes):
         # centres in, bucket + rank out (Morton pass); bucket, rank, offset in and ids out
         # (scatter)
         "bp_sort": 12 * nt + 8 * nt + 12 * nt + 4 * nt,
-        # ids, FP64 boxes and indices in; 64-B leaf records, FP32 leaf boxes (32 B) and the
+        # ids, FP64 boxes and indices in; 16-B leaf records, FP32 leaf boxes (32 B) and the
         # inner 4-ary levels (32 B per node, about nt/3 nodes) out
-        "bp_build": 4 * nt + 48 * nt + 12 * nt + 64 * nt + 32 * nt + 32 * nt // 3,
+        "bp_build": 4 * nt + 48 * nt + 12 * nt + 16 * nt + 32 * nt + 32 * nt // 3,
         # every leaf record and node box read once, each candidate pair (8 B) written once
-        "bp_traverse": 64 * nt + 32 * nt + 32 * nt // 3 + 8 * P,
+        "bp_traverse": 16 * nt + 32 * nt + 32 * nt // 3 + 8 * P,
         "screen_exact": 0,
         "derivs": H * (80 + 6 * 24 + 24 + 8 + s * 57),
         "assembly": 3 * s * nv + (9 * s + 4) * nnzb + 4 * (nv + 1) + H * 6 * 16 * 2,

@@ -10,8 +10,8 @@
 //                  rank inside its bucket from the counting atomic
 //   scan, scatter  counting sort of the triangles by bucket (order inside a bucket arbitrary)
 //   k_levels       an implicit complete 4-ary tree over the sorted leaves: node (l, k) covers
-//                  leaves [k 4^l, (k+1) 4^l); FP32 boxes (rounded outwards) are reduced level by
-//                  level in LDS, four levels per launch from the leaves, five per launch above,
+//                  leaves [k 4^l, (k+1) 4^l); FP32 boxes (rounded outwards) are reduced by waves
+//                  in registers, four levels per launch from the leaves, five per launch above,
 //                  so building needs no atomics and no fences.  The first launch also writes the
 //                  sorted leaves' vertex ids.  Each inner node also records a vertex all its
 //                  triangles hold, if there is one.
