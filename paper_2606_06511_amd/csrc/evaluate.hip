@@ -379,8 +379,9 @@ constexpr int kMergeChunks = 8;
 // work and no round of them is nearly empty.  Evaluations (162,000 candidates: the step) with 4096 blocks of five
 // waves a SIMD and chunks of one length, and now: 162,000 candidates 182 and 161 us, 184,000 85 and 65,
 // 2.0 M 134 and 127.5, 4.6 M (the step) 600 and 581, 20.8 M 515 and 489.  (1280 blocks of five waves: 160, 65, 129, 585,
-// 500.  Twice 1536 for long lists: 130 us for the 2.0 M, 481 for the 20.8 M.)
-constexpr int64_t kScreenBlocks = 1536;
+// 500.)  Twice that for a list that may be longer than kScreenLong, whose waves differ more: 20.8 M candidates
+// 493 and 480 us, 9 M 266 and 262; but 2.0 M 128.5 and 131, 162,000 163 and 166.
+constexpr int64_t kScreenBlocks = 1536, kScreenLong = 1 << 24;
 constexpr int kLate = 512;        // deferred candidates a wave gathers before it reserves their places
 constexpr int64_t kMaxUnits = 65536 * kWaves;  // entries of nfull: chunks of a 65536-block grid, or tiles
 
@@ -1494,7 +1495,8 @@ static hipError_t eval_impl(Ctx* c, const ttie_mesh* m, const int32_t* pairs, co
   stage_begin(c, TTIE_STAGE_SCREEN, s);
   // both screening kernels split the list the same way: the same grid
   const int64_t set = c->param[TTIE_PARAM_SCREEN_BLOCKS];
-  const unsigned gscreen = grid_for(pair_cap, (unsigned)(set ? set : kScreenBlocks));
+  const unsigned gscreen =
+      grid_for(pair_cap, (unsigned)(set ? set : pair_cap <= kScreenLong ? kScreenBlocks : 2 * kScreenBlocks));
   uint16_t* fsig = wsp<uint16_t>(c, L.fsig);
   // the screening's units: one chunk per wave, or tiles from a queue (at most kMaxUnits of
   // them, the length of nfull)

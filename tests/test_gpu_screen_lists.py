@@ -76,3 +76,24 @@ def test_chunks_of_the_list(n, blocks):
     ctx.check()
     assert np.array_equal(out["flags"].cpu().numpy(), ref[take])
     assert int(out["n_hits"].item()) == int((ref[take] == 1).sum())
+
+
+@pytest.mark.parametrize("capacity", [1 << 24, (1 << 24) + 1])
+def test_both_grids(capacity):
+    """On both sides of the pair capacity at which the screening's grid changes."""
+    import torch
+
+    from paper_2606_06511_amd import ttie, workloads
+
+    x, tris = workloads.folded_cloth(2, n=64)
+    pairs = oracle.pairs(x, tris)
+    ref = oracle.evaluate(x, tris, pairs, hessian=False)
+    ctx = ttie.Context(0)
+    ctx.reserve(len(x), len(tris), capacity, max_hits=1 << 12)
+    buf = torch.zeros((capacity, 2), dtype=torch.int32, device="cuda")
+    buf[: len(pairs)] = torch.from_numpy(pairs.astype(np.int32)).cuda()
+    out = ctx.evaluate(torch.from_numpy(x).cuda(), torch.from_numpy(tris).cuda(), buf,
+                       torch.tensor([len(pairs)], device="cuda"), hessian=False, flags=True)
+    ctx.check()
+    assert np.array_equal(out["flags"][: len(pairs)].cpu().numpy(), ref["flags"])
+    assert int(out["n_hits"].item()) == len(ref["hit_pair"]) > 0
