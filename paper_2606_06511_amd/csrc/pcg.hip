@@ -112,7 +112,8 @@ __device__ __forceinline__ int64_t diag_block(const int32_t* row_ptr, const int3
 
 // ---- the active rows ------------------------------------------------------------------------
 // flag[v] = row v holds blocks (row_ptr) or incidences of the last evaluation's hits; x, p = 0
-// on every row; a non-zero b on an inactive row latches STATUS_INVALID.  Row n's flag is 0 (the
+// on every row, and z, p2 (the other direction vector) on an inactive one, which a column of a
+// matrix whose pattern is not symmetric may name; a non-zero b there latches STATUS_INVALID.  Row n's flag is 0 (the
 // scan's total).  With off, each vertex's range in the evaluation's incidence lists is written
 // there too: off[v] = roff[number of touched vertices below v] for v in [0, n] (the touched
 // vertices are the rows, in vertex order, and roff their list starts), so that the range of v
@@ -122,7 +123,8 @@ __global__ void __launch_bounds__(kPB) k_pcg_flags(int64_t n, const int32_t* __r
                                                    const uint32_t* __restrict__ bm, const uint32_t* __restrict__ wp,
                                                    const int32_t* __restrict__ roff, int32_t* __restrict__ off,
                                                    const S* __restrict__ b, S* __restrict__ x, S* __restrict__ p,
-                                                   int32_t* __restrict__ flag, Counters* ctr) {
+                                                   S* __restrict__ z, S* __restrict__ p2, int32_t* __restrict__ flag,
+                                                   Counters* ctr) {
   for (int64_t v = (int64_t)blockIdx.x * kPB + threadIdx.x; v <= n; v += (int64_t)gridDim.x * kPB) {
     bool touched = false;
     if (off) {
@@ -144,7 +146,10 @@ __global__ void __launch_bounds__(kPB) k_pcg_flags(int64_t n, const int32_t* __r
       p[3 * v + c] = (S)0.0;
       nz |= (double)b[3 * v + c] != 0.0;
     }
-    if (!act && nz) atomicCAS(&ctr->status, 0, STATUS_INVALID);
+    if (act) continue;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) z[3 * v + c] = p2[3 * v + c] = (S)0.0;
+    if (nz) atomicCAS(&ctr->status, 0, STATUS_INVALID);
   }
 }
 
@@ -161,8 +166,8 @@ struct Active {
 };
 
 template <class S>
-static hipError_t pcg_active(Ctx* c, int64_t n, const int32_t* row_ptr, int32_t* off, const S* b, S* x, S* p,
-                             Active& a, hipStream_t s) {
+static hipError_t pcg_active(Ctx* c, int64_t n, const int32_t* row_ptr, int32_t* off, const S* b, S* x, S* p, S* z,
+                             S* p2, Active& a, hipStream_t s) {
   const Layout& L = c->L;
   int32_t* flag = wsp<int32_t>(c, L.pcg_flag);
   int32_t* pos = wsp<int32_t>(c, L.pcg_pos);
@@ -170,7 +175,7 @@ static hipError_t pcg_active(Ctx* c, int64_t n, const int32_t* row_ptr, int32_t*
   Counters* ctr = wsp<Counters>(c, L.counters);
   const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>(4096, (n + 1 + kPB - 1) / kPB));
   k_pcg_flags<S><<<g, kPB, 0, s>>>(n, row_ptr, wsp<uint32_t>(c, L.bm), wsp<uint32_t>(c, L.wp), wsp<int32_t>(c, L.roff),
-                                   off, b, x, p, flag, ctr);
+                                   off, b, x, p, z, p2, flag, ctr);
   hipError_t e = launch_scan_i32(c, flag, pos, n + 1, s);
   if (e != hipSuccess) return e;
   k_pcg_compact<<<g, kPB, 0, s>>>(n, flag, pos, act);
@@ -310,19 +315,6 @@ template <class S>
 __device__ __forceinline__ double direction(const S* __restrict__ z, const S* __restrict__ p, double beta, int64_t k) {
   return (double)(S)((double)z[k] + beta * (double)p[k]);
 }
-// A column without an active row of its own (of a matrix whose pattern is not symmetric) holds
-// zeros in every vector that the products read.
-template <class S>
-__device__ __forceinline__ void zero_inactive_columns(const int32_t* __restrict__ flag, const int32_t* __restrict__ row_ptr,
-                                                      const int32_t* __restrict__ col_idx, int64_t i, S* __restrict__ z,
-                                                      S* __restrict__ p2) {
-  for (int32_t k = row_ptr[i]; k < row_ptr[i + 1]; ++k) {
-    const int64_t c = col_idx[k];
-    if (flag[c]) continue;
-#pragma unroll
-    for (int e = 0; e < 3; ++e) z[3 * c + e] = p2[3 * c + e] = (S)0.0;
-  }
-}
 
 template <class S>
 __global__ void __launch_bounds__(kPB) k_pcg_diag(Active a, const int32_t* __restrict__ row_ptr,
@@ -341,14 +333,12 @@ __global__ void __launch_bounds__(kPB) k_pcg_diag(Active a, const int32_t* __res
 }
 
 template <class S>
-__global__ void __launch_bounds__(kPB) k_pcg_setup(Active a, const int32_t* __restrict__ flag,
-                                                   const int32_t* __restrict__ row_ptr,
+__global__ void __launch_bounds__(kPB) k_pcg_setup(Active a, const int32_t* __restrict__ row_ptr,
                                                    const int32_t* __restrict__ col_idx, const S* __restrict__ vals,
                                                    const S* __restrict__ b, double scale, S* __restrict__ r,
-                                                   S* __restrict__ z, S* __restrict__ p, S* __restrict__ p2,
-                                                   S* __restrict__ dinv, double mu_rel,
-                                                   const double* __restrict__ pdiag, double* __restrict__ pout,
-                                                   PcgState* st) {
+                                                   S* __restrict__ z, S* __restrict__ p, S* __restrict__ dinv,
+                                                   double mu_rel, const double* __restrict__ pdiag,
+                                                   double* __restrict__ pout, PcgState* st) {
   const double dsum = grid_sum(pdiag, 0), dcnt = grid_sum(pdiag, 1);
   // mu relative to the mean diagonal entry of the rows holding blocks (1 for an empty matrix)
   const double mu = mu_rel * (dcnt > 0.0 ? dsum / dcnt : 1.0);
@@ -356,7 +346,6 @@ __global__ void __launch_bounds__(kPB) k_pcg_setup(Active a, const int32_t* __re
   PCG_ROWS(j, a) {
     const int64_t i = a.rows[j];
     const int64_t d = diag_block(row_ptr, col_idx, i);
-    zero_inactive_columns(flag, row_ptr, col_idx, i, z, p2);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       const double dg = (d >= 0 ? (double)vals[9 * d + 4 * c] : 0.0) + mu;
@@ -611,20 +600,17 @@ __global__ void __launch_bounds__(kPR) k_pcg_rows_mf(Active a, const int32_t* __
 // ---- coupled variant: A = K + w H + mu I, K a caller's PSD BSR matrix (FP64) --------------
 // (the quasi-static objective's elastic Hessian), H applied from the hit records as above.
 // Jacobi diagonal: K's diagonal entries + w times H's + mu.
-__global__ void __launch_bounds__(kPB) k_pcg_setup_cp(Active a, const int32_t* __restrict__ flag,
-                                                      const int32_t* __restrict__ row_ptr,
+__global__ void __launch_bounds__(kPB) k_pcg_setup_cp(Active a, const int32_t* __restrict__ row_ptr,
                                                       const int32_t* __restrict__ col_idx,
                                                       const double* __restrict__ vals, double w, double mu,
                                                       const double* __restrict__ b, double scale,
                                                       double* __restrict__ r, double* __restrict__ z,
-                                                      double* __restrict__ p, double* __restrict__ p2,
-                                                      double* __restrict__ dinv, double* __restrict__ pout,
-                                                      PcgState* st) {
+                                                      double* __restrict__ p, double* __restrict__ dinv,
+                                                      double* __restrict__ pout, PcgState* st) {
   double rz = 0.0, bb = 0.0;
   PCG_ROWS(j, a) {
     const int64_t i = a.rows[j];
     const int64_t d = diag_block(row_ptr, col_idx, i);
-    zero_inactive_columns(flag, row_ptr, col_idx, i, z, p2);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       const double dg = (d >= 0 ? vals[9 * d + 4 * c] : 0.0) + w * dinv[3 * i + c] + mu;
@@ -763,11 +749,11 @@ static hipError_t pcg_impl(Ctx* c, int64_t n, const int32_t* row_ptr, const int3
   PcgBufs<S> B(c);
   stage_begin(c, TTIE_STAGE_PCG, s);
   Active a;
-  hipError_t e = pcg_active<S>(c, n, row_ptr, nullptr, b, x, B.p[0], a, s);
+  hipError_t e = pcg_active<S>(c, n, row_ptr, nullptr, b, x, B.p[0], B.z, B.p[1], a, s);
   if (e != hipSuccess) return e;
   k_pcg_diag<S><<<kPB, kPB, 0, s>>>(a, row_ptr, col_idx, vals, B.pdiag);
-  k_pcg_setup<S><<<kPB, kPB, 0, s>>>(a, wsp<int32_t>(c, c->L.pcg_flag), row_ptr, col_idx, vals, b, scale, B.r, B.z,
-                                     B.p[0], B.p[1], B.dinv, mu_rel, B.pdiag, B.pset, B.st);
+  k_pcg_setup<S><<<kPB, kPB, 0, s>>>(a, row_ptr, col_idx, vals, b, scale, B.r, B.z, B.p[0], B.dinv, mu_rel, B.pdiag,
+                                     B.pset, B.st);
   pcg_iterate<S>(a, B, b, scale, x, max_iter, info, s, [&](int it, const double* rz_old, const double* rz_new) {
     k_pcg_matvec<S><<<kPQ, kPR, 0, s>>>(a, row_ptr, col_idx, vals, B.z, B.p[it % 2], B.p[(it + 1) % 2], B.q, B.pq, rz_old,
                                         rz_new, B.pset, tol, it, B.st);
@@ -789,7 +775,7 @@ static hipError_t pcg_mf_impl(Ctx* c, int64_t n, const S* b, double scale, S* x,
   const uint32_t max_hits = (uint32_t)c->lim.max_hits;
   stage_begin(c, TTIE_STAGE_PCG, s);
   Active a;
-  hipError_t e = pcg_active<S>(c, n, nullptr, off, b, x, B.p[0], a, s);
+  hipError_t e = pcg_active<S>(c, n, nullptr, off, b, x, B.p[0], B.z, B.p[1], a, s);
   if (e != hipSuccess) return e;
   k_pcg_diag_mf<S><<<kPB, kPB, 0, s>>>(a, off, inc, recs, B.dinv, B.pdiag);
   k_pcg_setup_mf<S><<<kPB, kPB, 0, s>>>(a, b, scale, B.r, B.z, B.p[0], B.dinv, mu_rel, B.pdiag, B.pset, B.st);
@@ -815,11 +801,11 @@ hipError_t launch_pcg_coupled(Ctx* c, int64_t n, const int32_t* row_ptr, const i
   const uint32_t max_hits = (uint32_t)c->lim.max_hits;
   stage_begin(c, TTIE_STAGE_PCG, s);
   Active a;
-  hipError_t e = pcg_active<double>(c, n, row_ptr, off, b, x, B.p[0], a, s);
+  hipError_t e = pcg_active<double>(c, n, row_ptr, off, b, x, B.p[0], B.z, B.p[1], a, s);
   if (e != hipSuccess) return e;
   k_pcg_diag_mf<double><<<kPB, kPB, 0, s>>>(a, off, inc, recs, B.dinv, B.pdiag);  // raw diagonal of H into dinv
-  k_pcg_setup_cp<<<kPB, kPB, 0, s>>>(a, wsp<int32_t>(c, L.pcg_flag), row_ptr, col_idx, vals, w, mu, b, scale, B.r, B.z,
-                                     B.p[0], B.p[1], B.dinv, B.pset, B.st);
+  k_pcg_setup_cp<<<kPB, kPB, 0, s>>>(a, row_ptr, col_idx, vals, w, mu, b, scale, B.r, B.z, B.p[0], B.dinv, B.pset,
+                                     B.st);
   pcg_iterate<double>(a, B, b, scale, x, max_iter, info, s, [&](int it, const double* rz_old, const double* rz_new) {
     k_pcg_hits_mf<double><<<kPB, kPT, 0, s>>>(a, recs, ctr, max_hits, B.z, B.p[it % 2], B.p[(it + 1) % 2], hv, rz_old,
                                               rz_new, B.pset, tol, it, B.st);
