@@ -128,7 +128,9 @@ const char* ttie_version(void);
 const char* ttie_last_error(void);
 
 /* Creates a context bound to HIP device `device`.  TTIE_ERR_NO_DEVICE when no GPU is
- * visible (safe to call on a machine without one).  *out receives the context. */
+ * visible (safe to call on a machine without one).  *out receives the context, with 4 bytes of
+ * pinned host memory for ttie_get_status, which ttie_destroy frees (and may wait for the device
+ * to do so).  Both may be called while a stream is captured. */
 ttie_status ttie_create(int device, ttie_ctx** out);
 ttie_status ttie_destroy(ttie_ctx* ctx);
 

@@ -282,13 +282,19 @@ ttie_status ttie_destroy(ttie_ctx* ctx) {
     if (ctx->timers[k].stop) (void)hipEventDestroy(ctx->timers[k].stop);
   }
   for (int k = 0; k < ctx->n_pool; ++k) (void)hipEventDestroy(ctx->event_pool[k]);
+  hipError_t e;
   {
     DeviceGuard g(ctx->device);
-    (void)hipHostFree(ctx->status_pin);
+    // (as in ttie_create: a capture elsewhere does not concern this memory)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    e = hipHostFree(ctx->status_pin);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
   }
   free(ctx->timers);
   free(ctx->event_pool);
   delete ctx;
+  if (e != hipSuccess) return hip_fail(e, "ttie_destroy: host memory of the status");
   return TTIE_OK;
 }
 
