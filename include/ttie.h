@@ -372,9 +372,10 @@ ttie_status ttie_pcg_coupled(ttie_ctx* ctx, int64_t n_rows, const int32_t* row_p
  * bit for bit (the evaluation sums in pair-key order and a candidate set does not depend on
  * the order of emission); only the speed changes.  A value of 0 restores the default. */
 enum {
-  TTIE_PARAM_SCREEN_BLOCKS = 0, /* blocks of the screening kernels: 64 .. 65536 (default 4096, of which
-                                   an evaluation then takes 1536, or 3072 for a pair capacity above
-                                   2^24: what the chip holds at once, or twice that) */
+  TTIE_PARAM_SCREEN_BLOCKS = 0, /* the most blocks the screening kernels share a list among: 64 .. 65536
+                                   (default 4096).  A list of up to 2^22 candidates takes 1536 of
+                                   them, what the chip holds at once, a longer one 3072, so larger
+                                   values change nothing. */
   TTIE_PARAM_ROW_BLOCKS = 1,    /* blocks of ttie_bsr_symbolic's row kernel: 64 .. 65536 (default 2048) */
   TTIE_PARAM_TRAV_BUDGET = 2,   /* work of a traversal wave (three units for 16 nodes visited or 64
                                    pairs tested) before it hands the rest of its search to other

@@ -215,18 +215,38 @@ __device__ __forceinline__ int screen_stage1(int64_t p, const double* x, int64_t
   return STEP_FULL;
 }
 
+// Blocks among whose waves the screening kernels split a list: at most kScreenBlocks, as many as
+// the chip holds of k_screen (six waves a SIMD, for which it gives up 4 registers), so that none
+// starts without work and no round of them is nearly empty; twice that for a list of more than
+// kScreenLong candidates, whose waves differ more.  The length is the device's (a buffer is often
+// reserved for far more): blocks of the grid beyond that number take no part.
+// Energy and gradient with 1536 and 3072 blocks on spheres and cloths (us): 994,864 candidates 57.3
+// and 61.3, 1.6 M 108.3 and 110.3, 3.6 M 147.5 and 148.6, 5.9 M 187.8 and 185.9, 7.1 M 182.8 and
+// 175.1, 15.6 M 356 and 347, 18.7 M 496 and 468.  (1024: 58.2, 108.8, 154.1, 201.8, 195.7, 389, 554;
+// 4096 blocks of five waves a SIMD and chunks of one length: 184,000 candidates 85 us, now 65.)
+constexpr int64_t kScreenBlocks = 1536, kScreenLong = 1 << 22;
+__host__ __device__ __forceinline__ int64_t screen_blocks(int64_t np, int64_t grid) {
+  return np <= kScreenLong ? (grid < kScreenBlocks ? grid : kScreenBlocks)
+                           : (grid < 2 * kScreenBlocks ? grid : 2 * kScreenBlocks);
+}
+
 // The candidate list is split into one contiguous chunk per wave (the same split in all screening
-// kernels): batches of 64, of which every wave takes as many as the others or one more, spread over
-// the grid.  (Chunks of one length left up to half of the waves idle where that is a few batches.)  Blocks are renumbered so that each XCD screens a
-// contiguous range of the list (its L2 then sees one region of the mesh).
+// kernels): batches of 64, of which every wave takes as many as the others or one more.  (Chunks of
+// one length left up to half of the waves idle where that is a few batches.)  Blocks are renumbered
+// so that each XCD screens a contiguous range of the list (its L2 then sees one region of the mesh).
 __device__ __forceinline__ int64_t chunk_start(int64_t np, int64_t nw, int64_t w) {
   return min(np, (int64_t)((uint64_t)w * (uint64_t)((np + 63) / 64) / (uint64_t)nw) * 64);
 }
 __device__ __forceinline__ void wave_chunk(int64_t np, int64_t& beg, int64_t& end, int64_t& wid) {
-  const int64_t G = gridDim.x;
-  const int64_t lb = (G % 8 == 0) ? xcd_block(blockIdx.x, G) : (int64_t)blockIdx.x;
+  const int64_t G = screen_blocks(np, gridDim.x);
+  const bool part = blockIdx.x < G;
+  const int64_t lb = part && G % 8 == 0 ? xcd_block(blockIdx.x, G) : (int64_t)blockIdx.x;
   const int64_t nw = G * kWaves;
   wid = lb * kWaves + threadIdx.x / 64;
+  if (!part) {  // an empty chunk
+    beg = end = np;
+    return;
+  }
   beg = chunk_start(np, nw, wid);
   end = chunk_start(np, nw, wid + 1);
 }
@@ -374,29 +394,22 @@ __global__ void __launch_bounds__(kBlock) k_screen_flag(const double* __restrict
 // plane sides, so the plane distances are computed again for a hit only.  The deferred candidates
 // of the lists and its own it gathers in LDS, and appends to the one list of k_screen_exact.
 constexpr int kMergeChunks = 8;
-// Blocks of k_screen and k_screen_flag, where the caller sets no number: as many as the chip holds
-// of k_screen (six waves a SIMD, for which it gives up 4 registers), so that none starts without
-// work and no round of them is nearly empty.  Evaluations (162,000 candidates: the step) with 4096 blocks of five
-// waves a SIMD and chunks of one length, and now: 162,000 candidates 182 and 161 us, 184,000 85 and 65,
-// 2.0 M 134 and 127.5, 4.6 M (the step) 600 and 581, 20.8 M 515 and 489.  (1280 blocks of five waves: 160, 65, 129, 585,
-// 500.)  Twice that for a list that may be longer than kScreenLong, whose waves differ more: 20.8 M candidates
-// 493 and 480 us, 9 M 266 and 262; but 2.0 M 128.5 and 131, 162,000 163 and 166.
-constexpr int64_t kScreenBlocks = 1536, kScreenLong = 1 << 24;
 constexpr int kLate = 512;        // deferred candidates a wave gathers before it reserves their places
 constexpr int64_t kMaxUnits = 65536 * kWaves;  // entries of nfull: chunks of a 65536-block grid, or tiles
 
 __global__ void __launch_bounds__(kBlock) k_screen_full(const double* __restrict__ x, int64_t nv,
                                                         const int32_t* __restrict__ tris, int64_t nt,
                                                         const int32_t* __restrict__ pairs, const int64_t* n_pairs_dev,
-                                                        int64_t max_pairs, int64_t n_chunks, int64_t tile, double half,
-                                                        int va,
+                                                        int64_t max_pairs, int64_t screen_grid, int64_t tile,
+                                                        double half, int va,
                                                         HitGeom* __restrict__ hits, uint32_t max_hits,
                                                         int32_t* __restrict__ defer, const int32_t* __restrict__ full,
                                                         const uint16_t* __restrict__ fsig,
                                                         const int32_t* __restrict__ nfull, Counters* ctr,
                                                         uint8_t* __restrict__ flags, double* __restrict__ pair_T) {
   const int64_t np = min(*n_pairs_dev, max_pairs);
-  // the units: the tiles, or the chunks of the screening grid's n_chunks waves
+  // the units: the tiles, or the chunks of the screening's waves
+  const int64_t n_chunks = screen_blocks(np, screen_grid) * kWaves;
   const int64_t n_units = tile ? (np + tile - 1) / tile : n_chunks;
   const int lane = __lane_id();
   const int64_t c0 = ((int64_t)blockIdx.x * kWaves + threadIdx.x / 64) * kMergeChunks;
@@ -1525,10 +1538,9 @@ static hipError_t eval_impl(Ctx* c, const ttie_mesh* m, const int32_t* pairs, co
   const bool bsr = row_ptr != nullptr;
 
   stage_begin(c, TTIE_STAGE_SCREEN, s);
-  // both screening kernels split the list the same way: the same grid
-  const int64_t set = c->param[TTIE_PARAM_SCREEN_BLOCKS];
+  // both screening kernels split the list the same way: the same grid, enough for a full list
   const unsigned gscreen =
-      grid_for(pair_cap, (unsigned)(set ? set : pair_cap <= kScreenLong ? kScreenBlocks : 2 * kScreenBlocks));
+      grid_for(pair_cap, (unsigned)screen_blocks(pair_cap, ctx_param(c, TTIE_PARAM_SCREEN_BLOCKS)));
   uint16_t* fsig = wsp<uint16_t>(c, L.fsig);
   // the screening's units: one chunk per wave, or tiles from a queue (at most kMaxUnits of
   // them, the length of nfull)
@@ -1538,10 +1550,9 @@ static hipError_t eval_impl(Ctx* c, const ttie_mesh* m, const int32_t* pairs, co
                                       nfull, ctr, flags, pair_T, bm, nw, tile);
   k_screen_flag<<<gscreen, kBlock, 0, s>>>(m->x, nv, m->tris, pairs, n_pairs, pair_cap, full, fsig, nfull, flags,
                                            pair_T, tile);
-  const int64_t n_chunks = (int64_t)gscreen * kWaves;
-  const int64_t max_units = tile ? (pair_cap + tile - 1) / tile : n_chunks;
+  const int64_t max_units = tile ? (pair_cap + tile - 1) / tile : (int64_t)gscreen * kWaves;
   k_screen_full<<<(unsigned)std::max<int64_t>(1, (max_units + kWaves * kMergeChunks - 1) / (kWaves * kMergeChunks)),
-                  kBlock, 0, s>>>(m->x, nv, m->tris, m->n_tris, pairs, n_pairs, pair_cap, n_chunks, tile, half, va,
+                  kBlock, 0, s>>>(m->x, nv, m->tris, m->n_tris, pairs, n_pairs, pair_cap, gscreen, tile, half, va,
                                   hits, max_hits, defer, full, fsig, nfull, ctr, flags, pair_T);
   stage_end(c, TTIE_STAGE_SCREEN, s);
   stage_begin(c, TTIE_STAGE_SCREEN_EXACT, s);

@@ -1,0 +1,80 @@
+"""Launch parameters at their defaults: setting what ttie_get_param reports changes no launch, the
+autotuner's choices hold the defaults, and lists on both sides of the length at which the screening's
+split changes, whatever the buffer is reserved for."""
+
+import json
+
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def _launches(torch, path, run):
+    """(kernel, grid) of everything that run launches."""
+    torch.cuda.synchronize()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        run()
+        torch.cuda.synchronize()
+    prof.export_chrome_trace(str(path))
+    events = json.loads(path.read_text())["traceEvents"]
+    return [(e["name"], tuple(e["args"]["grid"])) for e in events if "grid" in e.get("args", {})]
+
+
+def test_reported_values_are_the_defaults(tmp_path):
+    import torch
+
+    from paper_2606_06511_amd import autotune, ttie, workloads
+
+    x, tris = workloads.folded_cloth(2, n=64)
+    xd, td = torch.from_numpy(x).cuda(), torch.from_numpy(tris).cuda()
+    ctx = ttie.Context(0)
+    ctx.reserve(len(x), len(tris), 1 << 21, max_hits=1 << 12)
+    pairs, n = ctx.broadphase(xd, td)
+    ctx.evaluate(xd, td, pairs, n)
+    ctx.check()
+
+    def run():
+        ctx.evaluate(xd, td, pairs, n)
+        ctx.bsr_symbolic(len(x))
+
+    default = _launches(torch, tmp_path / "a.json", run)
+    if not default:
+        pytest.skip("no kernel records in this environment")
+    for name, (pid, values) in autotune.SPACE.items():
+        assert ctx.get_param(pid) in values, name
+    for p in range(5):
+        ctx.set_param(p, ctx.get_param(p))
+    assert _launches(torch, tmp_path / "b.json", run) == default
+    ctx.set_param(ttie.PARAM_SCREEN_BLOCKS, 64)
+    assert ("k_screen", 64) in [(k.split("(")[0].split("::")[-1], g[0]) for k, g in _launches(torch, tmp_path / "c.json", run)]
+
+
+@pytest.mark.parametrize("blocks", [0, 64, 2000, 65536])
+@pytest.mark.parametrize("n", [1, 65, 64 * 6144 - 1, 1 << 22, (1 << 22) + 1, 64 * 12288 * 6 + 63])
+def test_lists_in_a_large_buffer(n, blocks):
+    """The split follows the list's length, not the buffer's: a short list in a large buffer, and both
+    sides of 2^22 candidates."""
+    import torch
+
+    from paper_2606_06511_amd import ttie, workloads
+
+    x, tris = workloads.folded_cloth(2, n=64)
+    pairs = oracle.pairs(x, tris).astype(np.int32)
+    ref = oracle.evaluate(x, tris, pairs, hessian=False)["flags"]
+    take = torch.from_numpy(np.random.default_rng(n).integers(0, len(pairs), n)).cuda()
+    want = torch.from_numpy(ref).cuda()[take]
+    cap = max(n, 5_000_000)
+    buf = torch.zeros((cap, 2), dtype=torch.int32, device="cuda")
+    buf[:n] = torch.from_numpy(pairs).cuda()[take]
+    hits = int((want == 1).sum().item())
+    ctx = ttie.Context(0)
+    ctx.reserve(len(x), len(tris), cap, max_hits=max(64, hits), max_blocks=64)
+    ctx.set_param(ttie.PARAM_SCREEN_BLOCKS, blocks)
+    out = ctx.evaluate(torch.from_numpy(x).cuda(), torch.from_numpy(tris).cuda(), buf,
+                       torch.tensor([n], device="cuda"), hessian=False, flags=True)
+    ctx.check()
+    assert torch.equal(out["flags"][:n], want)
+    assert int(out["n_hits"].item()) == hits
