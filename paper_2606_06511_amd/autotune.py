@@ -14,9 +14,10 @@ import torch
 
 from . import ttie
 
-# candidate values per parameter (the library's defaults are 4096, 2048, 128, 64 and 0)
+# candidate values per parameter, the library's default (4096, 2048, 128 and 0) among them; more
+# than 3072 screening blocks are never used
 SPACE = {
-    "screen_blocks": (ttie.PARAM_SCREEN_BLOCKS, (512, 1024, 2048, 4096, 8192)),
+    "screen_blocks": (ttie.PARAM_SCREEN_BLOCKS, (512, 1024, 1536, 4096)),
     "row_blocks": (ttie.PARAM_ROW_BLOCKS, (256, 512, 1024, 2048, 4096)),
     "trav_budget": (ttie.PARAM_TRAV_BUDGET, (16, 24, 32, 64, 128, 256, 1024)),
     # 0: one contiguous chunk of the candidate list per wave; otherwise tiles from a queue
