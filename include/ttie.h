@@ -379,7 +379,9 @@ enum {
   TTIE_PARAM_ROW_BLOCKS = 1,    /* blocks of ttie_bsr_symbolic's row kernel: 64 .. 65536 (default 2048) */
   TTIE_PARAM_TRAV_BUDGET = 2,   /* work of a traversal wave (three units for 16 nodes visited or 64
                                    pairs tested) before it hands the rest of its search to other
-                                   waves: 16 .. 2^20 (default 128) */
+                                   waves: 16 .. 2^20 (default 128, of which meshes of up to 2^19
+                                   triangles, with few waves, take half; a value that is set is
+                                   taken as it is for every mesh) */
   TTIE_PARAM_HASH_BUDGET = 3,   /* later bucket entries a hash thread tests before a whole wave takes
                                    over the rest: 16 .. 2^20 (default 64) */
   TTIE_PARAM_SCREEN_TILE = 4,   /* candidates per tile of the screening's tile queue: a multiple of
@@ -391,6 +393,7 @@ enum {
   TTIE_PARAM_COUNT = 5
 };
 ttie_status ttie_set_param(ttie_ctx* ctx, int param, int64_t value);
+/* the value set, or the default given above */
 ttie_status ttie_get_param(ttie_ctx* ctx, int param, int64_t* value_host);
 
 /* out = x + alpha * d for n_verts x 3 positions: x and out float64, d in `precision`.  A result

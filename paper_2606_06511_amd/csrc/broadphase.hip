@@ -575,7 +575,8 @@ constexpr uint32_t kGuard = (1u << 10) | (1u << 21) | (1u << 31);
 // Measured, broad phase of the 4,194,304-triangle sphere at 64, 96, 128, 192: 1.38, 1.25, 1.23,
 // 1.22 ms; of the 1,048,576-triangle one: 0.40, 0.39, 0.41, 0.43 ms.
 // With few groups -- all resident at once, or nearly: 5,120 waves are -- the kernel lasts as long as its
-// slowest wave while most of the chip is idle, so there the budget is halved, and while the second
+// slowest wave while most of the chip is idle, so there the default is half (a caller's budget is taken
+// as it is), and while the second
 // kernel has too few batches to fill the chip it takes each in four parts.  The broad phase of a
 // 36,000-triangle batch of three meshes of different sizes then takes 89 us instead of 168, of a
 // 126,000-triangle batch of six 113 instead of 160, of a 63,000-triangle sphere with fans at its poles 120
@@ -584,7 +585,7 @@ constexpr uint32_t kGuard = (1u << 10) | (1u << 21) | (1u << 31);
 // cloth costs 292 us instead of 278.  Four parts on spheres of 665,000 and 1,048,576 triangles: 297 us
 // instead of 331 and 393 instead of 415; on the cloth 276 instead of 274, on a 64-problem batch
 // and a sphere of 4,194,304 1.47 instead of 1.455 ms and 1.26 instead of 1.24.
-constexpr int64_t kTravFew = 1 << 19;    // triangles up to which the budget is halved
+constexpr int64_t kTravFew = 1 << 19;    // triangles up to which the default budget is half
 constexpr int64_t kTravParts = 1 << 20;  // and up to which batches are taken in parts
 // Queries overlapping one candidate from which adjacency is tested before the pairs are listed:
 // 64 more comparisons a batch, which pay where nearly the whole group shares a vertex with it.
@@ -1530,13 +1531,13 @@ hipError_t launch_broadphase(Ctx* c, const ttie_mesh* m, int method, const doubl
     const size_t half = L.bvh_heavy_bytes / 2 / 256 * 256;
     const TravHeavy heavy{wsp<TravNode>(c, L.bvh_heavy), wsp<TravBatch>(c, L.bvh_heavy + half),
                           (uint32_t)(half / sizeof(TravNode)), (uint32_t)(half / sizeof(TravBatch))};
-    const int budget = (int)ctx_param(c, TTIE_PARAM_TRAV_BUDGET);
+    const bool own = c->param[TTIE_PARAM_TRAV_BUDGET] != 0;  // set by the caller
+    const int budget = (int)ctx_param(c, TTIE_PARAM_TRAV_BUDGET) / (nt <= kTravFew && !own ? 2 : 1);
     const int32_t* qe = tri_off ? qend : nullptr;
     const auto traverse = va ? k_traverse<true> : k_traverse<false>;
     const auto traverse_heavy = va ? k_traverse_heavy<true> : k_traverse_heavy<false>;
     traverse<<<(unsigned)nb, kTravThreads, 0, s>>>(nt, lv, boxes, leaves, tbox, qe, heavy,
-                                                   nt <= kTravFew ? (budget + 1) / 2 : budget, pairs, capacity, npairs,
-                                                   ctr);
+                                                   budget, pairs, capacity, npairs, ctr);
     stage_end(c, TTIE_STAGE_BP_TRAVERSE, s);
     stage_begin(c, TTIE_STAGE_BP_HEAVY, s);
     traverse_heavy<<<1024, kTravThreads, 0, s>>>(nt, lv, boxes, leaves, tbox, qe, heavy, nt <= kTravParts ? 4 : 1, pairs,

@@ -78,3 +78,34 @@ def test_lists_in_a_large_buffer(n, blocks):
     ctx.check()
     assert torch.equal(out["flags"][:n], want)
     assert int(out["n_hits"].item()) == hits
+
+
+def test_a_set_budget_is_taken_as_it_is():
+    """Half of the default budget is what a mesh of few groups takes by itself: set, it hands over as
+    many batches of candidates (the workspace's tenth word; 3 % is several times what the arbitrary
+    order inside the sort's buckets changes), and the whole default fewer."""
+    import torch
+
+    from paper_2606_06511_amd import ttie
+
+    rng = np.random.default_rng(0)
+    n = 300_000
+    x = torch.from_numpy((rng.uniform(0.0, 42.0, (n, 1, 3)) + rng.normal(0.0, 0.4, (n, 3, 3))).reshape(-1, 3)).cuda()
+    tris = torch.arange(3 * n, dtype=torch.int32, device="cuda").reshape(n, 3)
+    ctx = ttie.Context(0)
+    ctx.reserve(3 * n, n, 8_000_000, max_hits=64)
+    head = -ctx.workspace.data_ptr() % 256
+
+    def batches(value):
+        ctx.set_param(ttie.PARAM_TRAV_BUDGET, value)
+        total = 0
+        for _ in range(4):
+            ctx.broadphase(x, tris)
+            ctx.check()
+            total += ctx.workspace[head : head + 40].view(torch.int32)[9].item()
+        return total
+
+    default = batches(0)
+    assert default > 1000
+    assert abs(batches(64) - default) <= 0.03 * default
+    assert batches(128) < 0.97 * default
