@@ -103,9 +103,14 @@ static Layout layout_with(const ttie_limits& lim, size_t scan_bytes, bool eval_o
   L.bvh_centroid = take_other(T * 3 * 4);
   L.bvh_part = take_other(512 * 6 * 4);
   L.bvh_ext = take_other(512 * 8);
-  // saved traversal states (32 B each) of the queries handed to the wave-cooperative kernel
-  L.bvh_heavy_bytes = (size_t)std::min<int64_t>(2 * T, (int64_t)1 << 20) * 32;
-  L.bvh_heavy = take_other(L.bvh_heavy_bytes);
+  // what the traversal hands over: nodes (a group of 64 leaves hands over its stack once, at most
+  // 256 entries), and batches of candidates, of which a heap of a few thousand triangles has
+  // thousands: of the 263 of a heap of 1500 only 176 fitted where 32 B a triangle were shared out,
+  // and the first kernel took 795 us with the others, now 82
+  L.trav_node_cap = (uint32_t)std::min<size_t>(256 * ((T + 63) / 64), (size_t)1 << 21);
+  L.trav_nodes = take_other(L.trav_node_cap * kTravNodeBytes);
+  L.trav_batch_cap = (uint32_t)std::min<size_t>(std::max<size_t>(T / 8, 1 << 13), (size_t)1 << 16);
+  L.trav_batches = take_other(L.trav_batch_cap * kTravBatchBytes);
   L.hash_grid = take_other(64);
   const size_t E = (size_t)kHashEntriesPerTri * T;
   L.hash_key = take_other(E * 8);

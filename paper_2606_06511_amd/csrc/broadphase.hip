@@ -604,6 +604,7 @@ struct __align__(16) TravBatch {
   int32_t group, count, pad[2];
   int32_t leaf[64];
 };
+static_assert(sizeof(TravNode) == kTravNodeBytes && sizeof(TravBatch) == kTravBatchBytes, "as the workspace is laid out");
 struct TravHeavy {
   TravNode* nodes;
   TravBatch* batches;
@@ -1527,10 +1528,8 @@ hipError_t launch_broadphase(Ctx* c, const ttie_mesh* m, int method, const doubl
     // a wave per 64 leaves, block count rounded up to a multiple of the 8 XCDs
     const int64_t per = kGroup * kTravWaves;
     const int64_t nb = ((nt + per - 1) / per + 7) / 8 * 8;
-    // half of the region for the nodes handed over, half for the batches
-    const size_t half = L.bvh_heavy_bytes / 2 / 256 * 256;
-    const TravHeavy heavy{wsp<TravNode>(c, L.bvh_heavy), wsp<TravBatch>(c, L.bvh_heavy + half),
-                          (uint32_t)(half / sizeof(TravNode)), (uint32_t)(half / sizeof(TravBatch))};
+    const TravHeavy heavy{wsp<TravNode>(c, L.trav_nodes), wsp<TravBatch>(c, L.trav_batches), L.trav_node_cap,
+                          L.trav_batch_cap};
     const bool own = c->param[TTIE_PARAM_TRAV_BUDGET] != 0;  // set by the caller
     const int budget = (int)ctx_param(c, TTIE_PARAM_TRAV_BUDGET) / (nt <= kTravFew && !own ? 2 : 1);
     const int32_t* qe = tri_off ? qend : nullptr;

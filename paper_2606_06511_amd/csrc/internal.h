@@ -117,6 +117,9 @@ __device__ __forceinline__ uint32_t wave_slot(bool want, uint32_t* counter) {
   return want ? base + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull)) : 0xffffffffu;
 }
 
+// bytes of a node and of a batch of candidates that the tree traversal hands over
+constexpr size_t kTravNodeBytes = 8, kTravBatchBytes = 272;
+
 struct Layout {
   size_t counters, hits, defer, recs, cnt, cur, off, ncol, inc, colbuf, cstage, hvbuf, epart_v, scan_tmp,
       scan_tmp_bytes;
@@ -128,8 +131,11 @@ struct Layout {
   size_t irow, csort, cval, colrun;
   // the first stage's exact plane sides of each candidate passed to the full screening
   size_t fsig;
-  size_t bvh_heavy, bvh_heavy_bytes, bvh_ext, hash_grid, hash_key, hash_tri, hash_rank, hash_skey, hash_stri, bvh_keys, bvh_qend, bvh_vals, bvh_vals2, bvh_hist, bvh_offset, bvh_boxes, bvh_leaves,
-      bvh_tbox, bvh_centroid, bvh_part, touched, inc2, pcg_vec, pcg_part, pcg_state, pcg_flag, pcg_pos, pcg_act;
+  // what the tree traversal hands over, and the room for it
+  size_t trav_nodes, trav_batches;
+  uint32_t trav_node_cap, trav_batch_cap;
+  size_t bvh_ext, hash_grid, hash_key, hash_tri, hash_rank, hash_skey, hash_stri, bvh_keys, bvh_qend, bvh_vals,
+      bvh_vals2, bvh_hist, bvh_offset, bvh_boxes, bvh_leaves, bvh_tbox, bvh_centroid, bvh_part, touched, inc2, pcg_vec, pcg_part, pcg_state, pcg_flag, pcg_pos, pcg_act;
   size_t total;
 };
 

@@ -1,0 +1,53 @@
+"""Small heaps in which every triangle overlaps nearly every other: what the few groups hand over has
+room, so the second kernel's waves share it."""
+
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def _heap(n):
+    rng = np.random.default_rng(n)
+    return rng.normal(0.0, 1.0, (3 * n, 3)), np.arange(3 * n, dtype=np.int32).reshape(n, 3)
+
+
+@pytest.mark.parametrize("n", [130, 700, 1500, 3000])
+def test_pairs_of_a_heap(n):
+    import torch
+
+    from paper_2606_06511_amd import ttie
+
+    x, tris = _heap(n)
+    ref = oracle.pairs(x, tris)
+    ctx = ttie.Context(0)
+    ctx.reserve(len(x), n, len(ref), max_hits=64)
+    pairs, k = ctx.broadphase(torch.from_numpy(x).cuda(), torch.from_numpy(tris).cuda(), ttie.BROAD_LBVH)
+    ctx.check()
+    got = pairs[: int(k.item())].cpu().numpy()
+    assert np.array_equal(got[np.lexsort((got[:, 1], got[:, 0]))], ref)
+
+
+def test_a_heap_is_shared_out():
+    """24 groups meet each other, 263 batches of candidates; the first kernel keeps 2016 of its own
+    group's combinations per wave (82 us, 795 us with the batches that found no room)."""
+    import torch
+
+    from paper_2606_06511_amd import ttie
+
+    x, tris = _heap(1500)
+    xd, td = torch.from_numpy(x).cuda(), torch.from_numpy(tris).cuda()
+    ctx = ttie.Context(0)
+    ctx.reserve(len(x), len(tris), 1_200_000, max_hits=64)
+    ms = []
+    ctx.broadphase(xd, td)
+    ctx.check()
+    ctx.set_timing(["bp_traverse"])
+    for _ in range(10):
+        ctx.broadphase(xd, td)
+        ctx.check()
+        ms.append(ctx.read_timers()["bp_traverse"][1])
+    ctx.set_timing([])
+    assert 0.0 < min(ms) < 0.3
