@@ -98,7 +98,9 @@ static Layout layout_with(const ttie_limits& lim, size_t scan_bytes, bool eval_o
   L.bvh_hist = take_other((size_t)kMaxBuckets * 4);
   L.bvh_offset = take_other(((size_t)kMaxBuckets + 1) * 4);
   L.bvh_boxes = take_other((2 * T + 64) * 32);  // implicit tree: at most 2T nodes of 32 B
-  L.bvh_leaves = take_other((T + 4) * 64);      // sorted leaf records, padded to a multiple of 4
+  // the sorted leaves' vertex ids and triangles, 16 B each, or a spring pattern's neighbour lists,
+  // 24 B a triangle
+  L.bvh_leaves = take_other(T * std::max(kLeafBytes, kSpringBytes));
   L.bvh_tbox = take_other(T * 6 * 8);
   L.bvh_centroid = take_other(T * 3 * 4);
   L.bvh_part = take_other(512 * 6 * 4);

@@ -294,6 +294,7 @@ struct __align__(16) LeafIds {
   int32_t v[3];
   int32_t tri;
 };
+static_assert(sizeof(LeafIds) == kLeafBytes, "as the workspace is laid out");
 
 __device__ __forceinline__ Box32 box_union(const Box32& a, const Box32& b) {
   Box32 r;
@@ -1408,8 +1409,8 @@ static unsigned bp_grid(int64_t n, unsigned cap = 4096) {
   return (unsigned)g;
 }
 
-// Every level is stored padded to a multiple of 4 nodes, so the four children of any node can
-// be loaded together without bounds checks (padding slots are never selected: c < m[l]).
+// Every level is stored padded to a multiple of 4 nodes, so a node's four children are one aligned
+// 128-byte line (the padding is neither written nor read: the search tests c < m[l] first).
 static int64_t pad4(int64_t m) { return (m + 3) & ~(int64_t)3; }
 
 Levels make_levels(int64_t n) {

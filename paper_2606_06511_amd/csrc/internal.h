@@ -119,6 +119,8 @@ __device__ __forceinline__ uint32_t wave_slot(bool want, uint32_t* counter) {
 
 // bytes of a node and of a batch of candidates that the tree traversal hands over
 constexpr size_t kTravNodeBytes = 8, kTravBatchBytes = 272;
+// and, a triangle, of its sorted leaves and of a spring pattern's neighbour lists (two ids an edge)
+constexpr size_t kLeafBytes = 16, kSpringBytes = 6 * sizeof(int32_t);
 
 struct Layout {
   size_t counters, hits, defer, recs, cnt, cur, off, ncol, inc, colbuf, cstage, hvbuf, epart_v, scan_tmp,

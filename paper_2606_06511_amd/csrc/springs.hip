@@ -120,7 +120,7 @@ hipError_t launch_springs_pattern(Ctx* c, const ttie_mesh* m, int32_t* row_ptr, 
   int32_t* off = wsp<int32_t>(c, L.off);
   int32_t* ucnt = wsp<int32_t>(c, L.ncol);
   // borrowed buffers: the evaluation's per-vertex counters and offsets, the broad phase's
-  // leaf records (6 entries per triangle, far below their size)
+  // leaves (whose region has room for kSpringBytes a triangle)
   int32_t* adj = wsp<int32_t>(c, L.bvh_leaves);
   k_sp_zero<<<sp_grid(nv + 1), kSB, 0, s>>>(deg, nv + 1);
   k_sp_zero<<<sp_grid(nv + 1), kSB, 0, s>>>(cur, nv + 1);
