@@ -576,18 +576,22 @@ constexpr uint32_t kGuard = (1u << 10) | (1u << 21) | (1u << 31);
 // Measured, broad phase of the 4,194,304-triangle sphere at 64, 96, 128, 192: 1.38, 1.25, 1.23,
 // 1.22 ms; of the 1,048,576-triangle one: 0.40, 0.39, 0.41, 0.43 ms.
 // With few groups -- all resident at once, or nearly: 5,120 waves are -- the kernel lasts as long as its
-// slowest wave while most of the chip is idle, so there the default is half (a caller's budget is taken
-// as it is), and while the second
-// kernel has too few batches to fill the chip it takes each in four parts.  The broad phase of a
-// 36,000-triangle batch of three meshes of different sizes then takes 89 us instead of 168, of a
-// 126,000-triangle batch of six 113 instead of 160, of a 63,000-triangle sphere with fans at its poles 120
-// instead of 157, of a 370,000-triangle one 270 instead of 308, of cloths of 130,000 and 149,000,
-// whose groups are alike, 93 instead of 96 and 93 instead of 90.  Half the budget on a 1,207,458-triangle
-// cloth costs 292 us instead of 278.  Four parts on spheres of 665,000 and 1,048,576 triangles: 297 us
-// instead of 331 and 393 instead of 415; on the cloth 276 instead of 274, on a 64-problem batch
-// and a sphere of 4,194,304 1.47 instead of 1.455 ms and 1.26 instead of 1.24.
-constexpr int64_t kTravFew = 1 << 19;    // triangles up to which the default budget is half
-constexpr int64_t kTravParts = 1 << 20;  // and up to which batches are taken in parts
+// slowest wave while most of the chip is idle, so there the default is half (a caller's budget is
+// taken as it is): 1.14 to 1.9 times shorter broad phases, with the parts below, on batches of 36,000
+// and 126,000 triangles and spheres of 63,000 and 370,000; on cloths of 130,000 and 149,000, whose
+// groups are alike, 93 us instead of 96 and 93 instead of 90; on one of 1,207,458 292 instead of 278.
+constexpr int64_t kTravFew = 1 << 19;  // triangles up to which the default budget is half
+// The second kernel takes each batch in four parts while what was handed over does not fill its
+// grid's waves: at most half as many nodes as waves (a node is a search of its own, which the parts
+// before it would delay) and twice as many batches.  Broad phase with whole batches and with four
+// parts, us (nodes, batches): spheres of 65,536 to 2,096,704 triangles 136 and 125 (16, 293), 199
+// and 179 (470, 1595), 397 and 374 (350, 1850), 515 and 494 (339, 2942), 706 and 693 (1204, 5727);
+// of 4,194,304 1164 and 1168 (3022, 10,088); heaps and mixed sizes 220 and 244 (2242, 678), 172 and
+// 181 (3753, 1842), 163 and 170 (4643, 1769); batches of 6, 20 and 64 problems 122 and 112 (1144,
+// 582), 194 and 201 (3381, 2503), 1195 and 1204 (7230, 3470).
+__device__ __forceinline__ int trav_parts(int64_t nodes, int64_t batches, int64_t waves) {
+  return 2 * nodes <= waves && batches <= 2 * waves ? 4 : 1;
+}
 // Queries overlapping one candidate from which adjacency is tested before the pairs are listed:
 // 64 more comparisons a batch, which pay where nearly the whole group shares a vertex with it.
 constexpr int kDense = 48;
@@ -1048,19 +1052,20 @@ __global__ void __launch_bounds__(kTravThreads, kTravMinWaves) k_traverse(int64_
   end_emit(em, sh, sink);
 }
 
-// What the waves over their budget handed over, a wave per node, batch or part of a batch (parts:
-// 1 or 4 of each).
+// What the waves over their budget handed over, a wave per batch, part of a batch or node.
 template <bool kVA>
 __global__ void __launch_bounds__(kTravThreads, kTravMinWaves) k_traverse_heavy(int64_t n64, Levels lv, const Box32* __restrict__ boxes,
                                                                  const LeafIds* __restrict__ leaves,
                                                                  const double* __restrict__ tbox,
                                                                  const int32_t* __restrict__ qend, TravHeavy heavy,
-                                                                 int parts, int32_t* pairs, int64_t cap,
+                                                                 int32_t* pairs, int64_t cap,
                                                                  unsigned long long* npairs, Counters* ctr) {
   __shared__ TravShared<PairEmitter> sh;
   const PairSink sink{pairs, cap, npairs, &ctr->status};
+  const int64_t batches = min(ctr->n_batches, heavy.batch_cap), nn = min(ctr->n_heavy, heavy.node_cap);
+  const int parts = trav_parts(nn, batches, (int64_t)gridDim.x * kTravWaves);
   const int most = 64 / parts;  // candidates of a batch that a wave takes
-  const int64_t nb = (int64_t)parts * min(ctr->n_batches, heavy.batch_cap), nn = min(ctr->n_heavy, heavy.node_cap);
+  const int64_t nb = parts * batches;
   if ((int64_t)blockIdx.x * kTravWaves >= nb + nn) return;  // (the whole block)
   level_table(sh, lv);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
@@ -1540,8 +1545,7 @@ hipError_t launch_broadphase(Ctx* c, const ttie_mesh* m, int method, const doubl
                                                    budget, pairs, capacity, npairs, ctr);
     stage_end(c, TTIE_STAGE_BP_TRAVERSE, s);
     stage_begin(c, TTIE_STAGE_BP_HEAVY, s);
-    traverse_heavy<<<1024, kTravThreads, 0, s>>>(nt, lv, boxes, leaves, tbox, qe, heavy, nt <= kTravParts ? 4 : 1, pairs,
-                                                 capacity, npairs, ctr);
+    traverse_heavy<<<1024, kTravThreads, 0, s>>>(nt, lv, boxes, leaves, tbox, qe, heavy, pairs, capacity, npairs, ctr);
     stage_end(c, TTIE_STAGE_BP_HEAVY, s);
   }
   return hipGetLastError();

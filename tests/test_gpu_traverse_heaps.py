@@ -51,3 +51,36 @@ def test_a_heap_is_shared_out():
         ms.append(ctx.read_timers()["bp_traverse"][1])
     ctx.set_timing([])
     assert 0.0 < min(ms) < 0.3
+
+
+@pytest.mark.parametrize("kind,whole", [("heap_1500", False), ("sphere_256", False), ("heap_3000", True),
+                                        ("sphere_2048", True)])
+def test_batches_whole_and_in_parts(kind, whole):
+    """On each side of the rule that splits batches (few nodes and batches were handed over; many
+    nodes; many batches), against the spatial hash's candidates, with no slot to spare."""
+    import torch
+
+    from paper_2606_06511_amd import ttie, workloads
+
+    n = int(kind.split("_")[1])
+    x, tris = _heap(n) if kind.startswith("heap") else workloads.noisy_sphere(1, n_lon=n, n_bands=n // 2 + 1)
+    xd, td = torch.from_numpy(x).cuda(), torch.from_numpy(tris).cuda()
+    ctx = ttie.Context(0)
+    ctx.reserve(len(x), len(tris), 16_000_000, max_hits=64)
+    keys = []
+    for method in (ttie.BROAD_BRUTE if kind.startswith("heap") else ttie.BROAD_HASH, ttie.BROAD_LBVH):
+        p, k = ctx.broadphase(xd, td, method)
+        ctx.check()
+        p = p[: int(k.item())].long()
+        keys.append(torch.sort(p[:, 0] * len(tris) + p[:, 1]).values)
+    head = -ctx.workspace.data_ptr() % 256
+    nodes, batches = ctx.workspace[head : head + 40].view(torch.int32)[8:].tolist()  # (handed over)
+    assert batches > 100 and (2 * nodes > 4096 or batches > 8192) == whole, (nodes, batches)
+    if kind.startswith("heap"):  # all pairs, of which the boxes of these overlap
+        i, j = keys[0] // len(tris), keys[0] % len(tris)
+        q = xd.reshape(-1, 3, 3)
+        lo, hi = q.amin(1), q.amax(1)
+        keys[0] = keys[0][((lo[i] <= hi[j]) & (lo[j] <= hi[i])).all(1)]
+    assert torch.equal(*keys)
+    p, k = ctx.broadphase(xd, td, ttie.BROAD_LBVH, capacity=len(keys[0]))
+    assert ctx.status() == ttie.TTIE_OK and int(k.item()) == len(keys[0])
