@@ -756,10 +756,11 @@ __device__ __forceinline__ void row_tests(uint32_t& bits, uint32_t qlo, uint32_t
   if constexpr (r < 12) row_tests<r + 4>(bits, qlo, qhi, clo, chi);
 }
 
-// kVA: pairs sharing exactly one vertex are candidates (a template argument, so the default
-// keeps the plain shared-vertex test).  kHeavy: the rest of a search handed over by another
-// wave: from the node `start`, or the tests of `most` candidates of `batch` from `first` on.
-template <bool kVA, bool kHeavy, class Emitter>
+// kVA: pairs sharing exactly one vertex are candidates; kBatch: the leaves are of several
+// problems, whose ends qend holds (template arguments, so the default keeps the plain tests and its
+// registers).  kHeavy: the rest of a search handed over by another wave: from the node `start`, or
+// the tests of `most` candidates of `batch` from `first` on.
+template <bool kVA, bool kBatch, bool kHeavy, class Emitter>
 __device__ __forceinline__ void search_group(TravWave& sh, const int32_t* lm, const uint32_t* loff, int32_t n, int L,
                                              int32_t g, uint32_t start, const TravBatch* batch, int first, int most,
                                              const Box32* __restrict__ boxes,
@@ -782,7 +783,7 @@ __device__ __forceinline__ void search_group(TravWave& sh, const int32_t* lm, co
   em.qtri = ql.tri;
   const float qeps = box_margin(qb);
   // leaves up to the end of the problem of the group's last leaf
-  const int32_t last = qend ? qend[s0 + nq - 1] : n;
+  const int32_t last = kBatch ? qend[s0 + nq - 1] : n;
   int nc = 0;          // candidates (uniform)
   int work = 0, steps = 0;  // steps of 16 nodes and of 64 pairs, three units each; steps of 16 nodes
 
@@ -803,6 +804,15 @@ __device__ __forceinline__ void search_group(TravWave& sh, const int32_t* lm, co
   // queries; own: the candidates are the queries, each paired with those before it
   const auto settle = [&](int cnt, bool own, int32_t leaf, const Box32& cb, const LeafIds& cl, uint32_t clo,
                           uint32_t chi) {
+    // in a group over the end of a problem a candidate's queries are those from the first one, f, of
+    // its own problem on (a batch of 1000 problems of 8 triangles in one place: 44 us, and 82 where
+    // all the group's overlaps were listed and tested one by one)
+    int f = 0;
+    if (kBatch && qend[s0] != last) {
+      const int32_t qe = qend[s0 + min(lane, nq - 1)];
+#pragma unroll
+      for (int b = 32; b > 0; b >>= 1) f += __shfl(qe, f + b - 1) <= leaf ? b : 0;
+    }
     uint32_t m[2];
     overlaps(clo, chi, m);
     // lanes past the last candidate, and a query's own leaf and those before it, do not count
@@ -812,6 +822,15 @@ __device__ __forceinline__ void search_group(TravWave& sh, const int32_t* lm, co
       // in the own row, ((i - r) & 15) < i iff 1 <= r <= i
       m[0] &= (0x7fffu & ~(0x7fffu >> li)) << 16 | before(1);
       m[1] &= before(2) << 16 | before(3);
+    }
+    if (kBatch && f > 0) {
+      // (the row's queries q from f on, as bit (15 - li + q) & 15: turned right by 1 + li)
+      const auto from = [&](int v) {
+        const uint32_t tail = (0xffffu << min(max(f - 16 * (row ^ v), 0), 16)) & 0xffffu;
+        return (tail * 0x10001u >> (1 + li)) & 0xffffu;
+      };
+      m[0] &= from(0) << 16 | from(1);
+      m[1] &= from(2) << 16 | from(3);
     }
     int p = __popc(m[0]) + __popc(m[1]);
     if (!kVA && __ballot(p >= kDense)) {
@@ -860,9 +879,7 @@ __device__ __forceinline__ void search_group(TravWave& sh, const int32_t* lm, co
         const int32_t av[3] = {__shfl(ql.v[0], j), __shfl(ql.v[1], j), __shfl(ql.v[2], j)};
         const int32_t bv[3] = {__shfl(cl.v[0], k), __shfl(cl.v[1], k), __shfl(cl.v[2], k)};
         const int32_t ta = __shfl(ql.tri, j), tb = __shfl(cl.tri, k);
-        const int32_t lb = __shfl(leaf, k);
         want = want && !(d < 0.0f) && !is_adjacent(av, bv, kVA);
-        if (qend) want = want && lb < qend[s0 + j];  // a group over the end of a problem
         if (want && !(d >= eps)) {
           // within the rounding of the FP32 boxes: the FP64 ones decide
           const double* A = tbox + 6 * (int64_t)ta;
@@ -1033,7 +1050,7 @@ __device__ __forceinline__ void end_emit(Emitter& em, Shared& sh, const PairSink
   em.store(base, o);
 }
 
-template <bool kVA>
+template <bool kVA, bool kBatch>
 __global__ void __launch_bounds__(kTravThreads, kTravMinWaves) k_traverse(int64_t n64, Levels lv, const Box32* __restrict__ boxes,
                                                            const LeafIds* __restrict__ leaves,
                                                            const double* __restrict__ tbox,
@@ -1047,13 +1064,13 @@ __global__ void __launch_bounds__(kTravThreads, kTravMinWaves) k_traverse(int64_
   const int64_t g = xcd_block(blockIdx.x, gridDim.x) * kTravWaves + wave;
   GroupEmitter em{&sh.stage[wave], 0, 0};
   if (g * kGroup < n64)
-    search_group<kVA, false>(sh.w[wave], sh.lm, sh.loff, (int32_t)n64, lv.L, (int32_t)g, 0u, nullptr, 0, 0, boxes,
+    search_group<kVA, kBatch, false>(sh.w[wave], sh.lm, sh.loff, (int32_t)n64, lv.L, (int32_t)g, 0u, nullptr, 0, 0, boxes,
                              leaves, tbox, qend, heavy, budget, em, sink, ctr);
   end_emit(em, sh, sink);
 }
 
 // What the waves over their budget handed over, a wave per batch, part of a batch or node.
-template <bool kVA>
+template <bool kVA, bool kBatch>
 __global__ void __launch_bounds__(kTravThreads, kTravMinWaves) k_traverse_heavy(int64_t n64, Levels lv, const Box32* __restrict__ boxes,
                                                                  const LeafIds* __restrict__ leaves,
                                                                  const double* __restrict__ tbox,
@@ -1073,7 +1090,7 @@ __global__ void __launch_bounds__(kTravThreads, kTravMinWaves) k_traverse_heavy(
   for (int64_t i = (int64_t)blockIdx.x * kTravWaves + wave; i < nb + nn; i += (int64_t)gridDim.x * kTravWaves) {
     const TravBatch* batch = i < nb ? heavy.batches + i / parts : nullptr;
     const TravNode node = i < nb ? TravNode{batch->group, 0u} : heavy.nodes[i - nb];
-    search_group<kVA, true>(sh.w[wave], sh.lm, sh.loff, (int32_t)n64, lv.L, node.group, node.node, batch,
+    search_group<kVA, kBatch, true>(sh.w[wave], sh.lm, sh.loff, (int32_t)n64, lv.L, node.group, node.node, batch,
                             (int)(i % parts) * most, most, boxes, leaves, tbox, qend, heavy, 0, em, sink, ctr);
   }
   end_emit(em, sh, sink);
@@ -1538,14 +1555,15 @@ hipError_t launch_broadphase(Ctx* c, const ttie_mesh* m, int method, const doubl
                           L.trav_batch_cap};
     const bool own = c->param[TTIE_PARAM_TRAV_BUDGET] != 0;  // set by the caller
     const int budget = (int)ctx_param(c, TTIE_PARAM_TRAV_BUDGET) / (nt <= kTravFew && !own ? 2 : 1);
-    const int32_t* qe = tri_off ? qend : nullptr;
-    const auto traverse = va ? k_traverse<true> : k_traverse<false>;
-    const auto traverse_heavy = va ? k_traverse_heavy<true> : k_traverse_heavy<false>;
-    traverse<<<(unsigned)nb, kTravThreads, 0, s>>>(nt, lv, boxes, leaves, tbox, qe, heavy,
+    // (the batch's broad phase has no vertex-adjacent option)
+    const auto traverse = tri_off ? k_traverse<false, true> : va ? k_traverse<true, false> : k_traverse<false, false>;
+    const auto traverse_heavy =
+        tri_off ? k_traverse_heavy<false, true> : va ? k_traverse_heavy<true, false> : k_traverse_heavy<false, false>;
+    traverse<<<(unsigned)nb, kTravThreads, 0, s>>>(nt, lv, boxes, leaves, tbox, qend, heavy,
                                                    budget, pairs, capacity, npairs, ctr);
     stage_end(c, TTIE_STAGE_BP_TRAVERSE, s);
     stage_begin(c, TTIE_STAGE_BP_HEAVY, s);
-    traverse_heavy<<<1024, kTravThreads, 0, s>>>(nt, lv, boxes, leaves, tbox, qe, heavy, pairs, capacity, npairs, ctr);
+    traverse_heavy<<<1024, kTravThreads, 0, s>>>(nt, lv, boxes, leaves, tbox, qend, heavy, pairs, capacity, npairs, ctr);
     stage_end(c, TTIE_STAGE_BP_HEAVY, s);
   }
   return hipGetLastError();
