@@ -58,24 +58,19 @@ FLUSH_BYTES = 1 << 30
 MEASURED = {
     # the screening kernels (k_screen, k_screen_flag, k_screen_full), 4,194,304-triangle sphere
     "screen": [
-        {"bytes": 572544683, "valu_wave": 78731139, "tcp_accesses": 152781216, "params": {"screen_blocks": 4096, "screen_tile": 0},
+        {"bytes": 614828198, "valu_wave": 77014735, "tcp_accesses": 129554713,
+         "params": {"screen_blocks": 4096, "screen_tile": 0},
          "sources": {
-             "paper_2606_06511_amd/csrc/evaluate.hip": "56f61dd399e314b14b02833e811c690b4b5f79691f3e4dc9f783489f3f79c76d",
-             "paper_2606_06511_amd/csrc/pair.h": "3214cbbbfc3adb8bb21bbd5a4ee7d42e551980c8d14782361af7c442d4b87904",
+             "paper_2606_06511_amd/csrc/evaluate.hip": "9ad7ab643941b725a22728382f3d41f9e3982bea87b4470d2355214ed9ef39c6",
+             "paper_2606_06511_amd/csrc/pair.h": "81cc412ad1e0f7c4d5fd2b9539e6d45f68049bf87607760f2d618efcb3d3398c",
              "paper_2606_06511_amd/csrc/predicates.h":
-                 "3dae2f86b3e306a1ff3a8053680aef2da3a8efdcbc81ab88b515de9126bd9a42"}},
-        {"bytes": 533334670, "valu_wave": 82897012, "tcp_accesses": 153007571, "params": {"screen_blocks": 8192, "screen_tile": 0},
-         "sources": {
-             "paper_2606_06511_amd/csrc/evaluate.hip": "56f61dd399e314b14b02833e811c690b4b5f79691f3e4dc9f783489f3f79c76d",
-             "paper_2606_06511_amd/csrc/pair.h": "3214cbbbfc3adb8bb21bbd5a4ee7d42e551980c8d14782361af7c442d4b87904",
-             "paper_2606_06511_amd/csrc/predicates.h":
-                 "3dae2f86b3e306a1ff3a8053680aef2da3a8efdcbc81ab88b515de9126bd9a42"}},
+                 "c338a8f4dbbc376adeb997d540a9c008fa85bc60756ed4de48cdc825bf4d9ef5"}},
     ],
 }
 # VALU issue peak: 256 CUs x 4 SIMD16 units x 2.4 GHz (a wave64 instruction takes a SIMD 4 cycles)
 VALU_LANE_PEAK = 256 * 4 * 16 * 2.4e9
 # L1 tag-access rate if each CU's vector L1 takes one tag lookup per clock (the gather kernels
-# measure 0.76-0.88 of it; a streaming fill 0.18)
+# measure 0.61-0.74 of it; a streaming fill 0.18)
 TCP_ACCESS_PEAK = 256 * 2.4e9
 
 

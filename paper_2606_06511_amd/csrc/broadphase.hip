@@ -537,8 +537,8 @@ __device__ __forceinline__ void block_flush(WaveEmitter<kCap>& em, int* wcount, 
 // test and are emitted.  On the noisy spheres a group visits about 100 nodes, meets about 120
 // candidates besides its own leaves and keeps about 750 of their 11,000 combinations.
 //
-// Bound by instruction issue (3,300 to 3,600 VALU instructions a group, half of the issue
-// peak) and the latency of the node loads.  With a depth-first search per leaf, whose waves lasted
+// Bound by instruction issue (on a 4,194,304-triangle sphere of 16.3 M candidates 3,860 VALU
+// instructions a group, 60% of the issue peak) and the latency of the node loads.  With a depth-first search per leaf, whose waves lasted
 // as long as their slowest lane's chain of dependent visits, the two kernels took 4.05 ms on a
 // 4,194,304-triangle sphere of 20.8 M candidates, now 0.97 ms; 0.98 and 0.28 ms on a
 // 1,048,576-triangle sphere of 4.6 M, 97 and 56 us on a 130,050-triangle cloth.  (Persistent waves,
